@@ -5,13 +5,14 @@ Workload: the ResNet-shaped layer 8x56x56x64 -> 64 kernels 3x3, stride 1,
 pad 1, inputs rounded to the 9-bit format (wE, wF) = (5, 3), multiply and
 accumulate in (5, 4) (the paper's HOBFLOPS9 MAC), fixed accumulation order
 (ky, kx, c). One step is the whole path on one batch: quantise + pack the
-float32 IFM and weights into bit-planes, then the bitsliced convolution, whose
-epilogue writes the OFM as float32 (the unpack fused in). Inputs are
+float32 IFM and weights into bit-planes, then the convolution in the kernel the
+library picks, whose epilogue writes the OFM as float32 (the unpack fused in). Inputs are
 synthetic, seeded, resident in HBM before timing starts.
 
 Prints one JSON line: GMAC/s of the step, the convolution kernel against the
-VALU roofline (achieved 32-bit bitwise VALU lane-ops/s from the generated
-netlist's instruction count and the kernel's HIP-event time), and the CPU
+VALU roofline (achieved 32-bit VALU lane-ops/s from the kernel's instruction
+count per MAC and its HIP-event time), the bitsliced kernel on the same layer
+against the same roofline, and the CPU
 oracle timed on a bounded sample of the same outputs.
 """
 import argparse
@@ -55,7 +56,7 @@ IN_FMT, ACC_FMT, OUT_FMT = (5, 3), (5, 4), (5, 4)
 # counter reads for a plain 256 MiB device copy (FETCH x2.0, WRITE x1.0); see
 # the profiles/ summaries. Set to None whenever the kernel changes, until the
 # counters are taken again.
-TRAFFIC = (3552.3 * 2.0 + 6276.3 * 1.0) * 1024   # 13.70 MB (split kernel, float32 OFM)
+TRAFFIC = None
 
 
 def log(*a):
@@ -126,12 +127,15 @@ def _time(fn, reps, stream):
     return e0.elapsed_time(e1) / reps
 
 
-KERNEL_NAME = {1: "fused", 2: "split", 3: "split_compact"}
+KERNEL_NAME = {0: "value", 1: "fused", 2: "split", 3: "split_compact"}
+VALUE = 0  # the kernel on float32 values
 
 
 def _conv_ops(d):
-    """(kernel shape the library runs d in, VALU ops per 32-MAC word of that
-    kernel)."""
+    """(kernel the library runs d in, VALU ops per 32 MACs of that kernel)."""
+    per_value = hf.conv2d_value_ops(d)
+    if per_value:
+        return VALUE, 32 * per_value
     algo = hf.conv2d_algo(d)
     ops = hf.netlist_ops((d.in_fmt.wE, d.in_fmt.wF), (d.acc_fmt.wE, d.acc_fmt.wF), d.round)
     return algo, (ops["mac"] if algo == hf.ALGO_FUSED else ops["mul"] + ops["accum"])
@@ -145,7 +149,10 @@ def issue_ceiling(d, algo):
     the time is at least taps x adder instructions x ISSUE_CLOCKS. Fused
     kernel: a wave's taps x MAC instructions x ISSUE_CLOCKS, or its SIMD's
     share of all waves x SIMD_CLOCKS per instruction when several share one
-    (workgroups of four waves spread over a CU's four SIMDs)."""
+    (workgroups of four waves spread over a CU's four SIMDs). The kernel on
+    values has no such limit of its own: 1."""
+    if algo == VALUE:
+        return 1.0
     OH, OW = hf.conv_out_hw(d)
     P, taps = d.N * OH * OW, d.KH * d.KW * d.C
     chain_waves = ((P + 63) // 64) * ((d.M + 31) // 32)
@@ -405,8 +412,6 @@ def sweep(reps):
             o = hf.conv2d(pi, pw, d)
             ms = _time(lambda: hf.conv2d(pi, pw, d, out=o), reps, stream)
             algo, G = _conv_ops(d)
-            if G == 0:  # no split kernel for this type: the library ran the fused one
-                algo, G = hf.ALGO_FUSED, ops["mac"]
             lane_ops = s.macs / 32.0 * G
             print(json.dumps({
                 "type": tname, "in": [wE, wi], "acc": [wE, wa], "round": V.RND_NAME[rnd],
@@ -480,15 +485,13 @@ def main():
     s = I.RESNET_CONV_SHAPE
     ifm, w = I.resnet_conv_inputs()
     P = s.N * s.OH * s.OW
-    # the library's automatic choice of kernel shape (for this layer: split
-    # multiply/accumulate waves, its accumulator waves leaving each SIMD at
-    # most one)
-    algo = hf.conv2d_algo(hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad,
-                                       IN_FMT, ACC_FMT, OUT_FMT, hf.ACT_NONE, hf.ALGO_AUTO))
-    # the last (here: only) layer writes float32 directly: the unpack is fused
-    # into the convolution's epilogue
-    d = hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad, IN_FMT, ACC_FMT,
-                     OUT_FMT, hf.ACT_NONE, algo, ofm_kind=hf.OFM_F32)
+    # the library's automatic choice of kernel; the last (here: only) layer
+    # writes float32 directly: the unpack is fused into the convolution's epilogue
+    def desc(choice, kind):
+        return hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad, IN_FMT, ACC_FMT,
+                            OUT_FMT, hf.ACT_NONE, choice, ofm_kind=kind)
+    d = desc(hf.ALGO_AUTO, hf.OFM_F32)
+    algo, G = _conv_ops(d)
     x_ifm = torch.from_numpy(ifm.reshape(s.N * s.H * s.W, s.C)).to(dev)
     x_w = torch.from_numpy(w.reshape(s.KH * s.KW * s.C, s.M)).to(dev)
     p_ifm = torch.empty(hf.plane_shape(s.N * s.H * s.W, s.C, IN_FMT), dtype=torch.int32, device=dev)
@@ -534,16 +537,19 @@ def main():
     conv_ms = float(np.mean([e[1].elapsed_time(e[2]) for e in evs]))
 
     macs = s.macs
-    ops = hf.netlist_ops(IN_FMT, ACC_FMT)
-    G = ops["mac"] if algo == hf.ALGO_FUSED else ops["mul"] + ops["accum"]
-    lane_ops = macs / 32.0 * G          # 32 MACs per 32-bit word operation
+    lane_ops = macs / 32.0 * G
     achieved = lane_ops / (conv_ms * 1e-3)
     ceiling = issue_ceiling(d, algo)
     pack_bytes = (s.N * s.H * s.W * s.C + s.KH * s.KW * s.C * s.M) * 4 + \
         (p_ifm.numel() + p_w.numel()) * 4
-    d_codes = hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad, IN_FMT, ACC_FMT,
-                           OUT_FMT, hf.ACT_NONE, algo, ofm_kind=hf.OFM_CODE)
-    codes = hf.conv2d(p_ifm, p_w, d_codes)  # the same outputs as codes, for the CPU check
+    # the bitsliced kernel on the same layer
+    d_bits = desc(hf.conv2d_algo(d), hf.OFM_F32)
+    ops = hf.netlist_ops(IN_FMT, ACC_FMT)
+    bits_ops = ops["mac"] if d_bits.algo == hf.ALGO_FUSED else ops["mul"] + ops["accum"]
+    bits_ms = _time(lambda: hf.conv2d(p_ifm, p_w, d_bits, out=y), args.steps, stream)
+    bits_rate = macs / 32.0 * bits_ops / (bits_ms * 1e-3)
+    # the same outputs as codes, for the CPU check
+    codes = hf.conv2d(p_ifm, p_w, desc(hf.ALGO_AUTO, hf.OFM_CODE))
     torch.cuda.synchronize()
     gpu_codes = codes.cpu().numpy().view(np.uint32).astype(np.uint64).reshape(s.N, s.OH, s.OW, s.M)
 
@@ -558,7 +564,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "e5m3 in, e5m4 acc, bitsliced on u32 planes",
+        "dtype": "e5m3 in, e5m4 acc, on u32 bit-planes",
         "data": "synthetic (seeded): IFM |N(0,1)| half zeroed, weights N(0,0.05)",
         "config": {"workload": "MCMK conv 8x56x56x64 -> 64 kernels 3x3, stride 1, pad 1, "
                                "HOBFLOPS9 (5,3)->(5,4), order (ky,kx,c); step = pack float32 IFM "
@@ -566,15 +572,19 @@ def main():
                                "fused into the epilogue)",
                    "macs_per_step": macs, "batch": s.N},
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_LANE_OPS / 1e12,
-                     "unit": "T VALU-op/s (32-bit bitwise, one op = 32 gates)",
+                     "unit": "T VALU-op/s (32-bit lane operations)",
                      "frac": achieved / PEAK_LANE_OPS, "traffic": TRAFFIC,
-                     "kernel": {1: "conv2d_kernel", 2: "conv2d_split_kernel",
+                     "kernel": {VALUE: "conv2d_value_kernel", 1: "conv2d_kernel",
+                                2: "conv2d_split_kernel",
                                 3: "conv2d_split_compact_kernel"}[algo],
                      "ops_per_mac_word": G,
                      "kernel_ms": conv_ms,
                      "issue_ceiling": ceiling},
         "pct_valu_peak": 100.0 * achieved / PEAK_LANE_OPS,
         "conv_gmacs": macs / (conv_ms * 1e-3) / 1e9,
+        "bitsliced": {"kernel": KERNEL_NAME[d_bits.algo], "kernel_ms": bits_ms,
+                      "gmacs": macs / (bits_ms * 1e-3) / 1e9, "ops_per_mac_word": bits_ops,
+                      "pct_valu_peak": 100.0 * bits_rate / PEAK_LANE_OPS},
         "pack_ms": pack_ms,
         "pack_gbps": pack_bytes / (pack_ms * 1e-3) / 1e9,
     }

@@ -47,8 +47,8 @@
  *    unpack fused into the last layer's epilogue, Sec. 3.4);
  *  - hobflops_netlist_ops reports the fused MAC, the multiplier, the
  *    accumulating adder and the element-wise MAC separately;
- *  - hobflops_pack_batch, hobflops_avgpool, hobflops_conv2d_algo and the
- *    *_supported queries are additions.
+ *  - hobflops_pack_batch, hobflops_avgpool, hobflops_conv2d_algo,
+ *    hobflops_conv2d_value_ops and the *_supported queries are additions.
  */
 #ifndef HOBFLOPS_H
 #define HOBFLOPS_H
@@ -90,7 +90,9 @@ enum { HOBFLOPS_ACT_NONE = 0, HOBFLOPS_ACT_RELU = 1 };
  * pairs per SIMD, two products per hand-over). AUTO picks SPLIT when the
  * launch has at most one accumulator wave (64 positions of one 32-kernel
  * tile) per SIMD of the device, SPLIT_COMPACT (else SPLIT) when it has at most
- * two, and FUSED otherwise. */
+ * two, and FUSED otherwise; and in the place of any of them a kernel that
+ * computes the same results on float32 values, one per lane, where that is
+ * estimated to be faster (hobflops_conv2d_value_ops). */
 enum {
   HOBFLOPS_ALGO_AUTO = 0,
   HOBFLOPS_ALGO_FUSED = 1,
@@ -180,13 +182,20 @@ int hobflops_conv2d(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
  * mode and (for HOBFLOPS_ALGO_SPLIT and _SPLIT_COMPACT) kernel shape, else 0. */
 int hobflops_conv2d_supported(const hobflops_conv_desc* d);
 
-/* The kernel shape hobflops_conv2d runs d in (HOBFLOPS_ALGO_FUSED, _SPLIT or
+/* The bitsliced kernel shape of d (HOBFLOPS_ALGO_FUSED, _SPLIT or
  * _SPLIT_COMPACT): d->algo itself, or for HOBFLOPS_ALGO_AUTO the shape AUTO
- * picks on the current device. Returns that value (>= 1), or a negative
+ * picks on the current device unless it runs d on float32 values
+ * (hobflops_conv2d_value_ops). Returns that value (>= 1), or a negative
  * status: HOBFLOPS_EINVAL for a bad descriptor, HOBFLOPS_EUNSUPPORTED where
  * hobflops_conv2d_supported is 0, HOBFLOPS_EHIP if AUTO cannot query the
  * device. Launches nothing. */
 int hobflops_conv2d_algo(const hobflops_conv_desc* d);
+
+/* Whether AUTO runs d on float32 values, one per lane, instead of bitsliced
+ * (the results are the same bits): the operations of one multiply-add there
+ * (float64 ones counted twice) if so, 0 if it runs bitsliced or d->algo names
+ * a shape, or a negative status as hobflops_conv2d_algo. Launches nothing. */
+int hobflops_conv2d_value_ops(const hobflops_conv_desc* d);
 
 /* Element-wise r = add(widen(c), mul(a, b)) over n elements of flat PL32
  * tensors (rows 1, len n): a, b, c in in_fmt, r in acc_fmt (same wE,

@@ -374,6 +374,19 @@ def split_asm(wE, wi, wa, rnd, cache, compact=False):
     return cache[key] if cache[key]["text"] is not None else None
 
 
+def value_ops(wi, wa, rnd):
+    """Operations of one multiply-add of the kernel on float32 values
+    (csrc/value.hpp, ValueMath), float64 ones counted twice: the product, its
+    rounding unless it is exact, the sum and its rounding."""
+    exact = wa >= 2 * wi + 1
+    if rnd == variants.RTZ:
+        return 3 if exact else 4
+    if wa > 10:
+        return 11 if exact else 14
+    lift = not exact and 23 - wa < 15
+    return 5 if exact else 8 if lift else 7
+
+
 def generate(verbose=True):
     os.makedirs(GEN, exist_ok=True)
     compact_excluded = _compact_excluded()
@@ -480,6 +493,7 @@ def generate(verbose=True):
         src = f"""// Generated: convolution variant {tag}. Do not edit.
 #include "kernels.hpp"
 #include "registry.hpp"
+#include "value.hpp"
 namespace hobflops {{
 namespace conv_{tag} {{
 {cache[mac]['text']}
@@ -490,7 +504,8 @@ namespace conv_{tag} {{
 {compact_text}
 struct V {{
   static constexpr int NIN = {nb(wE, wi)}, NACC = {nb(wE, wa)}, NOUT = {nb(wE, wo)};
-  static constexpr int wE = {wE}, wF_OUT = {wo};
+  static constexpr int wE = {wE}, wF_IN = {wi}, wF_ACC = {wa}, wF_OUT = {wo};
+  static constexpr int kAct = {act}, kRound = {rnd};
 {split_members}  static __device__ __forceinline__ void mac(uint32_t (&acc)[NACC], const uint32_t (&w)[NIN],
                                              const uint32_t (&x)[NIN]) {{ {mac}(acc, w, x); }}
   static __device__ __forceinline__ void mul(const uint32_t (&w)[NIN], const uint32_t (&x)[NIN],
@@ -505,6 +520,7 @@ struct V {{
 {compact_struct}}}  // namespace conv_{tag}
 hipError_t launch_conv_{tag}(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
                               const ConvParams& p, int algo, hipStream_t stream) {{
+  if (algo >= kAlgoValue) return launch_value<conv_{tag}::V>(ifm, w, ofm, p, algo - kAlgoValue, stream);
   dim3 grid((unsigned)((p.P + kConvBlock - 1) / kConvBlock), (unsigned)p.MT);
 {split_launch}    hipLaunchKernelGGL(conv2d_kernel<conv_{tag}::V>, grid, dim3(kConvBlock), 0, stream, ifm, w, ofm, p);
   return hipGetLastError();
@@ -591,7 +607,8 @@ hipError_t launch_pool_{tag}(const uint32_t* in, uint32_t* out, const PoolParams
     reg.append("const ConvVariant kConvVariants[] = {")
     for v, tag, ops, pops, aops, has_split, has_compact in reg_conv:
         reg.append(f"  {{{v[0]}, {v[1]}, {v[2]}, {v[3]}, {v[4]}, {v[5]}, {has_split}, "
-                   f"{has_compact}, {ops}, {pops}, {aops}, launch_conv_{tag}}},")
+                   f"{has_compact}, {ops}, {pops}, {aops}, {value_ops(*v[1:3], v[5])}, "
+                   f"launch_conv_{tag}}},")
     reg.append("};")
     reg.append(f"const int kNumConvVariants = {len(reg_conv)};")
     reg.append("const MuladdVariant kMuladdVariants[] = {")

@@ -213,13 +213,15 @@ int hobflops_unpack(const uint32_t* planes, int64_t rows, int64_t len, hobflops_
 // workgroups (or the split kernel in two rounds where the compact form was
 // not generated). More: the fused kernel, whose waves fill the SIMDs by
 // themselves.
-static int resolve_algo(const hobflops_conv_desc* d, const ConvVariant* v, int* algo) {
+static int resolve_algo(const hobflops_conv_desc* d, const ConvVariant* v, int* algo,
+                        int* device_cus = nullptr) {
   *algo = d->algo;
   if (d->algo != HOBFLOPS_ALGO_AUTO) return HOBFLOPS_OK;
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return hip_status(e);
+  if (device_cus) *device_cus = cus;
   const int64_t OH = (d->H + 2 * (int64_t)d->pad - d->KH) / d->stride + 1;
   const int64_t OW = (d->W + 2 * (int64_t)d->pad - d->KW) / d->stride + 1;
   const int64_t P = (int64_t)d->N * OH * OW;
@@ -234,6 +236,95 @@ static int resolve_algo(const hobflops_conv_desc* d, const ConvVariant* v, int* 
   else
     *algo = HOBFLOPS_ALGO_FUSED;
   return HOBFLOPS_OK;
+}
+
+// AUTO's choice between the bitsliced kernel shape `algo` and the kernel on
+// float32 values: the tile of the latter, or -1. Both sides are estimated in
+// microseconds from the layer's sizes and the variant's operation counts; every
+// constant below was measured on MI355X (256 CUs) and is not sensitive.
+//  - On values, a workgroup computes one tile; tiles beyond the number of CUs
+//    take further rounds. A round costs `chains` accumulator chains a SIMD, at
+//    1.26 ns a tap and operation each (112x64 tiles: 8x56x56x64 -> 64, 576 taps
+//    of 7 operations in 142 us, one round), a part of each tap that does not
+//    shrink with the tile (staging and waits: 7x7 and 14x14 layers at batch 1
+//    and 16), and a start and an end (1x1 layers).
+//  - Bitsliced: one chain wave per SIMD or fewer: a tap costs the adder's
+//    instructions at 2.09 ns (159 us for 576 taps of 134); up to two: both
+//    netlists' at 2.48 ns in the compact kernel, or two rounds of the split one;
+//    more: the chip's share of the fused netlist at 1.73 ns an instruction
+//    (4x224x224x3 -> 64: 73 us).
+// The 16x32 and 32x32 tiles alone handle fewer than kFlatC channels. Byte
+// offsets in that kernel are 32 bits wide.
+static int value_plan(const ConvParams& p, const ConvVariant& v, int algo, int cus) {
+  const int64_t nin = 3 + v.wE + v.wF_in, taps = (int64_t)p.KH * p.KW * p.C;
+  if ((int64_t)p.N * p.H * p.W * p.CG * nin >= (int64_t)1 << 29 ||
+      taps * p.MT * nin >= (int64_t)1 << 29)
+    return -1;
+  const double t = (double)taps;
+  struct Tile {
+    int pos, mtiles, chains;
+    double tap_ns, fixed_us;
+  };
+  static const Tile kTiles[] = {
+      {112, 2, 28, 0.0, 11.0}, {56, 2, 14, 10.0, 6.0}, {32, 2, 8, 13.0, 4.0},
+      {32, 1, 4, 18.0, 3.0},   {16, 1, 2, 20.0, 2.5}};
+  int best = -1;
+  double best_us = 0.0;
+  for (int k = p.C < kFlatC ? kTile32x32 : 0; k <= kTile16x32; ++k) {
+    const Tile& q = kTiles[k];
+    const int64_t n = (((int64_t)p.P + q.pos - 1) / q.pos) * ((p.MT + q.mtiles - 1) / q.mtiles);
+    const double rounds = (double)((n + cus - 1) / cus);
+    const double us = rounds * (t * (q.chains * 1.26 * v.value_ops + q.tap_ns) * 1e-3 + q.fixed_us);
+    if (best < 0 || us < best_us) {
+      best = k;
+      best_us = us;
+    }
+  }
+  const double waves = (double)(((int64_t)p.P + 63) / 64 * p.MT), simds = 4.0 * cus;
+  double tap_ns;
+  if (algo == HOBFLOPS_ALGO_FUSED) {
+    const double share = waves / simds;
+    tap_ns = v.mac_ops * 1.73 * (share > 2.0 ? share : 2.0);
+  } else if (algo == HOBFLOPS_ALGO_SPLIT_COMPACT) {
+    tap_ns = (v.mul_ops + v.accum_ops) * 2.48;
+  } else {
+    tap_ns = v.accum_ops * 2.09 * (waves > simds ? 2.0 : 1.0);
+  }
+  return best_us < t * tap_ns * 1e-3 + 4.0 ? best : -1;
+}
+
+// The kernel's parameters of a checked descriptor (those that come with the
+// call's pointers are set by hobflops_conv2d).
+static ConvParams conv_params(const hobflops_conv_desc* d) {
+  ConvParams p{};
+  p.N = d->N;
+  p.H = d->H;
+  p.W = d->W;
+  p.C = d->C;
+  p.M = d->M;
+  p.KH = d->KH;
+  p.KW = d->KW;
+  p.stride = d->stride;
+  p.pad = d->pad;
+  p.OH = (d->H + 2 * d->pad - d->KH) / d->stride + 1;
+  p.OW = (d->W + 2 * d->pad - d->KW) / d->stride + 1;
+  p.CG = (d->C + 31) / 32;
+  p.MT = (d->M + 31) / 32;
+  p.P = p.N * p.OH * p.OW;
+  p.ofm_kind = d->ofm_kind;
+  return p;
+}
+
+int hobflops_conv2d_value_ops(const hobflops_conv_desc* d) {
+  const int st = conv_check(d);
+  if (st != HOBFLOPS_OK) return st;
+  const ConvVariant* v = find_conv(d);
+  if (!v) return HOBFLOPS_EUNSUPPORTED;
+  if (d->algo != HOBFLOPS_ALGO_AUTO) return 0;
+  int algo = 0, cus = 0;
+  const int st2 = resolve_algo(d, v, &algo, &cus);
+  if (st2 != HOBFLOPS_OK) return st2;
+  return value_plan(conv_params(d), *v, algo, cus) >= 0 ? v->value_ops : 0;
 }
 
 int hobflops_conv2d_algo(const hobflops_conv_desc* d) {
@@ -265,36 +356,25 @@ int hobflops_conv2d(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
   if (!v || (d->algo == HOBFLOPS_ALGO_SPLIT && !v->has_split) ||
       (d->algo == HOBFLOPS_ALGO_SPLIT_COMPACT && !v->has_compact))
     return HOBFLOPS_EUNSUPPORTED;
-  ConvParams p;
-  p.N = d->N;
-  p.H = d->H;
-  p.W = d->W;
-  p.C = d->C;
-  p.M = d->M;
-  p.KH = d->KH;
-  p.KW = d->KW;
-  p.stride = d->stride;
-  p.pad = d->pad;
-  p.OH = (d->H + 2 * d->pad - d->KH) / d->stride + 1;
-  p.OW = (d->W + 2 * d->pad - d->KW) / d->stride + 1;
-  p.CG = (d->C + 31) / 32;
-  p.MT = (d->M + 31) / 32;
-  p.P = p.N * p.OH * p.OW;
-  p.ofm_kind = d->ofm_kind;
+  ConvParams p = conv_params(d);
   p.ofm_vec = ((uintptr_t)ofm & 15u) == 0;
   p.spin_cap = g_spin_cap.load(std::memory_order_relaxed);
   {
     const hipError_t e = wait_fail_word(&p.wait_fail);
     if (e != hipSuccess) return hip_status(e);
   }
-  int algo = 0;
+  int algo = 0, cus = 0;
   {
-    const int st2 = resolve_algo(d, v, &algo);
+    const int st2 = resolve_algo(d, v, &algo, &cus);
     if (st2 != HOBFLOPS_OK) return st2;
   }
-  const int kalgo = algo == HOBFLOPS_ALGO_SPLIT           ? kAlgoSplit
-                    : algo == HOBFLOPS_ALGO_SPLIT_COMPACT ? kAlgoSplitCompact
-                                                          : kAlgoFused;
+  int kalgo = algo == HOBFLOPS_ALGO_SPLIT           ? kAlgoSplit
+              : algo == HOBFLOPS_ALGO_SPLIT_COMPACT ? kAlgoSplitCompact
+                                                    : kAlgoFused;
+  if (d->algo == HOBFLOPS_ALGO_AUTO) {
+    const int tile = value_plan(p, *v, algo, cus);
+    if (tile >= 0) kalgo = kAlgoValue + tile;
+  }
   return hip_status(v->launch(ifm, w, ofm, p, kalgo, (hipStream_t)stream));
 }
 

@@ -127,6 +127,11 @@ constexpr uint32_t kSpinCap = 1u << 20;
 
 // Kernel shapes of the convolution (hobflops_conv_desc.algo).
 constexpr int kAlgoAuto = 0, kAlgoFused = 1, kAlgoSplit = 2, kAlgoSplitCompact = 3;
+// The kernel on float32 values (value.hpp), which AUTO takes where it is the
+// faster one: kAlgoValue + tile, a tile of positions x kernels a workgroup.
+constexpr int kAlgoValue = 4;
+constexpr int kTile112x64 = 0, kTile56x64 = 1, kTile32x64 = 2, kTile32x32 = 3, kTile16x32 = 4;
+constexpr int kFlatC = 16;  // fewer channels than this: chunks of taps across pixels
 
 
 // MCMK convolution (paper Sec. 3.4). One lane owns one output position and

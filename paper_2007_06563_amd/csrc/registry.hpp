@@ -21,6 +21,7 @@ struct ConvVariant {
   int mac_ops;    // VALU bitwise instructions of one fused multiply-add step
   int mul_ops;    // ... of the multiplier alone (split kernel, multiplier waves)
   int accum_ops;  // ... of the accumulating adder alone (split kernel, adder waves)
+  int value_ops;  // float32 operations of one multiply-add on values (float64 ones counted twice)
   conv_launch_fn launch;
 };
 

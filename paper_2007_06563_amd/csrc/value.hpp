@@ -1,0 +1,562 @@
+// MCMK convolution on float32 values: the same arithmetic as the bitsliced
+// kernels (kernels.hpp), bit for bit, computed one value per lane instead of
+// 32 per word.
+//
+// Why: a bitsliced MAC of (5,3) -> (5,4) takes 203 instructions per 32 values,
+// 6.3 a value, and its smallest piece of work is a wave of 2,048 accumulator
+// chains that no reordering may split; a layer of a few hundred such waves
+// leaves most of the chip idle. One float32 operation per step of the MAC takes
+// 7 instructions a value (4 rounding toward zero) whatever the fraction width,
+// and its smallest piece is 64 chains.
+//
+// How float32 gives the format's own results. A value of (wE, wF) is an exact
+// float32. Operands are scaled by powers of two, so that the format's smallest
+// normal number is float32's, 2^-126, in products and sums.
+//  - Product. With K = 2^k + 1, k = 23 - wF_acc: c = RN(K w x),
+//    d = RN(c - w x), r = c - d is the product rounded to wF_acc fraction bits
+//    (Veltkamp's splitting). w x has at most 2 (wF_in + 1) <= 22 bits, so 2^k w x
+//    is an even multiple of c's last place and c's own rounding, ties to even,
+//    is the one asked for; d is then exactly 2^k w x. K w (or K x) is exact.
+//    Types whose products are exact in the accumulator skip this.
+//  - Sum. s = RN(acc + r) in float32, then the same splitting of s. Rounding
+//    twice gives the single rounding's result for the sum of two numbers of p
+//    bits when the first rounding keeps at least 2p + 1 bits: p = wF_acc + 1
+//    <= 11. Ties of the second rounding have p + 1 bits, so the argument above
+//    holds for them too.
+//    Wider accumulators rounding to nearest are held and added in float64 (53
+//    bits: p <= 26), split by the same steps.
+//  - Toward zero, float32's own rounding is set toward zero and the bits below
+//    the format's last place are cleared; truncating twice is exact for any p.
+//  - Underflow. The hardware mode flushes float32 results below 2^-126 to a
+//    zero of their sign: the rounded product r is produced by a subtraction
+//    whose exact result it is, so it is flushed after rounding as the format
+//    asks, and a sum below the smallest normal number is always exact, so
+//    flushing it before rounding is the same.
+//  - Zero signs are IEEE's in every step.
+//  - Overflow and inputs that are infinite or NaN do not fit this: a workgroup
+//    that meets such an input, or whose inputs are so large that a sum could
+//    leave the format's range, computes its tile again step by step with the
+//    range checks written out (mac_checked).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "codec.hpp"
+#include "kernels.hpp"
+#include "lanes.hpp"
+
+#pragma clang fp contract(off)
+
+namespace hobflops {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) float lds_f32;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+
+__device__ __forceinline__ float pow2f(int e) { return __int_as_float((e + 127) << 23); }
+
+// The arithmetic of one variant V (wE, wF_IN, wF_ACC, wF_OUT, kRound, kAct).
+template <class V>
+struct ValueMath {
+  static constexpr int wE = V::wE, wI = V::wF_IN, wA = V::wF_ACC;
+  static constexpr bool kRtz = V::kRound != 0;
+  static constexpr bool kExact = wA >= 2 * wI + 1;  // products are exact in the accumulator
+  static constexpr bool kWide = !kRtz && wA > 10;   // sums in float64
+  using Acc = typename std::conditional<kWide, double, float>::type;
+  static constexpr int kBias = (1 << (wE - 1)) - 1;
+  // products and sums are scaled by 2^kScale, IFM values by 2^kScaleX
+  static constexpr int kScale = -126 + kBias, kScaleX = kScale / 2;
+  static constexpr int k = 23 - wA;
+  static constexpr uint32_t kMask = ~((1u << k) - 1u);
+  // The smallest nonzero product is 2^(-126 - kBias) scaled; where 2^k times it
+  // would be flushed, c and d are formed 2^kLift larger and r scaled back (one
+  // more instruction): a flushed d beside a normal c would not cancel.
+  static constexpr int kLift = kRtz || kExact || k >= kBias ? 0 : kBias - k;
+  static constexpr int kScaleW = kScale - kScaleX + kLift;
+  // exponent of the first power of two out of range
+  static constexpr int kTop = (1 << wE) - kBias;
+  // A narrow exponent range under a long fraction (2^(wF+2) times a product of
+  // up to 2^3 leaves the range): no useful bound of the sums follows from the
+  // largest operands, so the largest sum is tracked (half an instruction a MAC).
+  static constexpr bool kTrack = wE < 5 && wA + 5 > kTop;
+
+  // MODE: float32 rounding nearest or toward zero; float32 and float64 results
+  // below the smallest normal number flushed, such operands read as they are
+  // (bits 5:4 and 7:6 = 1).
+  static __device__ __forceinline__ void set_mode() {
+    __builtin_amdgcn_s_setreg(1 | (0 << 6) | (7 << 11), 0x50 | (kRtz ? 3 : 0));
+  }
+  static __device__ __forceinline__ float trunc(float v) {
+    return __uint_as_float(__float_as_uint(v) & kMask);
+  }
+  // the multiplier's second form of a weight: K w
+  static __device__ __forceinline__ float prescale(float w) {
+    return kRtz || kExact ? w : w * (float)((1 << k) + 1);
+  }
+  static __device__ __forceinline__ float product(float w, float wk, float x) {
+    if constexpr (kRtz) return kExact ? w * x : trunc(w * x);
+    if constexpr (kExact) return w * x;
+    const float c = wk * x;
+    const float d = __builtin_fmaf(-w, x, c);
+    const float r = c - d;
+    return kLift ? r * pow2f(-kLift) : r;
+  }
+  // acc + r in the format; a float64 accumulator is scaled by 2^-896 more, so
+  // that 2^-1022 is the format's smallest normal number
+  static __device__ __forceinline__ Acc add(Acc acc, float r, float& track) {
+    if constexpr (kWide) {
+      const double s = __builtin_fma((double)r, 0x1p-896, acc);
+      const double u = s * (double)((1LL << (52 - wA)) + 1);
+      const double v = u - s;
+      return u - v;
+    } else {
+      const float s = acc + r;
+      if constexpr (kTrack) asm("v_max_f32 %0, %1, |%2|" : "=v"(track) : "v"(track), "v"(s));
+      if constexpr (kRtz) return trunc(s);
+      const float u = s * (float)((1 << k) + 1);
+      const float v = u - s;
+      return u - v;
+    }
+  }
+  // the accumulator's value, unscaled (exact)
+  static __device__ __forceinline__ float value(Acc acc) {
+    if constexpr (kWide) return (float)(acc * __builtin_ldexp(1.0, 896 - kScale));
+    return acc * pow2f(-kScale);
+  }
+  // The same step on unscaled values with every check written out: infinities
+  // and NaN follow IEEE-754, overflow gives a signed infinity.
+  static __device__ __forceinline__ float range(float v) {
+    uint32_t b = __float_as_uint(v);
+    const uint32_t a = b & 0x7FFFFFFFu, s = b & 0x80000000u;
+    b = a < (uint32_t)(127 - kBias) << 23 ? s : b;
+    b = a >= (uint32_t)(127 + kTop) << 23 && a <= 0x7F800000u ? s | 0x7F800000u : b;
+    return __uint_as_float(b);
+  }
+  static __device__ __forceinline__ float round_checked(float v) {
+    uint32_t b = __float_as_uint(v);
+    if constexpr (!kRtz) b += ((b >> k) & 1u) + ((1u << (k - 1)) - 1u);
+    return range(__uint_as_float((b & kMask) | (v != v ? 0x7FC00000u : 0u)));
+  }
+  static __device__ __forceinline__ float mac_checked(float acc, float w, float x) {
+    const float r = round_checked((w * pow2f(-kScaleX - kScaleW)) * x);
+    if constexpr (kWide) {
+      const double s = (double)acc + (double)r;
+      const double u = s * (double)((1LL << (52 - wA)) + 1);
+      const double v = u - s;
+      return s - s == 0.0 ? range((float)(u - v)) : (float)s;  // infinite and NaN sums as they are
+    } else {
+      return round_checked(acc + r);
+    }
+  }
+};
+
+// Code -> float32 scaled by 2^scale. kChecked: infinities and NaN as
+// float32's; otherwise such codes give some number (the caller looks for them).
+template <int wE, int wF, int kScale, bool kChecked>
+__device__ __forceinline__ uint32_t decode_scaled(uint32_t code) {
+  constexpr int sh_s = wF + wE;
+  constexpr uint32_t bias = (uint32_t)(127 - ((1 << (wE - 1)) - 1) + kScale) << 23;
+  const uint32_t v = (__builtin_amdgcn_ubfe(code, 0, sh_s) << (23 - wF)) + bias;
+  const uint32_t x0 = (uint32_t)__builtin_amdgcn_sbfe((int)code, sh_s + 1, 1);
+  uint32_t mag = x0 & v;
+  if constexpr (kChecked) {
+    const uint32_t x1 = (uint32_t)__builtin_amdgcn_sbfe((int)code, sh_s + 2, 1);
+    mag = x1 ? 0x7F800000u | (x0 & 0x00400000u) : mag;
+  }
+  // v_bfi: the sign bit from the shifted code
+  return __builtin_amdgcn_bitop3_b32(0x7FFFFFFFu, mag, code << (31 - sh_s), 0xCA);
+}
+
+constexpr int kRow = 36;  // floats of an LDS row: 32 taps, rows 16-byte aligned, 4 banks apart
+
+// A workgroup of WP x WM waves computes 2 RP WP positions x 32 RM WM kernels.
+// A wave holds RM m-tiles x 2 RP positions: lane j of half h kernel j of each
+// m-tile and positions h RP .. h RP + RP - 1, RM * RP chains a lane.
+//
+// Taps are taken in the fixed order in chunks of at most 32: the channels of
+// one (ky, kx, channel word), or, where a channel word holds fewer than
+// kFlatC channels, 32 consecutive taps across pixels. For a chunk the workgroup
+// turns the plane words of its positions and weight rows into float32 values
+// in LDS ([position][tap] and [kernel][tap]); every MAC operand is then read
+// four taps at a time, an IFM value as a broadcast within each half wave. The
+// words of the next chunk are loaded while this one is computed, and the LDS
+// tiles are double buffered, so there is one barrier a chunk. A chunk is filled
+// up to a multiple of four taps with w = -0, x = +0: adding -0 changes nothing.
+//
+// Staging goes by sets of four 32-value groups, one per row of 16 lanes, a
+// plane word a lane (two where a code has more than 16 bits), through the
+// lane transpose; a set leaves two words a lane.
+template <class V, int RM, int RP, int WP, int WM>
+struct ValueTile {
+  static constexpr int kWaves = WP * WM, kThreads = 64 * kWaves;
+  static constexpr int kPos = 2 * RP * WP, kKern = 32 * RM * WM;
+  static constexpr int kXSets = (kPos + 3) / 4, kWSets = kKern / 4;
+  static constexpr int XS = (kXSets + kWaves - 1) / kWaves, WS = (kWSets + kWaves - 1) / kWaves;
+};
+
+template <class V, bool kFlat, int RM, int RP, int WP, int WM>
+__global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
+    const uint32_t* __restrict__ ifm, const uint32_t* __restrict__ w, uint32_t* __restrict__ ofm,
+    ConvParams p, float bound) {
+  using T = ValueTile<V, RM, RP, WP, WM>;
+  using A = ValueMath<V>;
+  constexpr int NIN = V::NIN, NOUT = V::NOUT, XS = T::XS, WS = T::WS, NW = T::kWaves;
+  constexpr bool kHigh = NIN > 16;  // a second plane word a lane
+  __shared__ float xs[2][T::kXSets * 4][kRow];
+  __shared__ float ws[2][T::kKern][kRow];
+  __shared__ uint32_t largest[4];  // magnitudes of x and w, largest sum, any infinity or NaN
+
+  const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wp = wave % WP, wm = wave / WP;
+  const int p0 = blockIdx.x * T::kPos, mt0 = blockIdx.y * (RM * WM);
+  const int taps = p.KH * p.KW * p.C;
+  const int nch = kFlat ? (taps + 31) / 32 : p.KH * p.KW * p.CG;
+  if (tid < 4) largest[tid] = 0u;
+
+  // staging: this lane's group of a set, and its plane
+  const int row = lane >> 4, l = lane & 15;
+  const int grp = ((row & 1) << 1) | (row >> 1);
+  const RowT rt = row_transpose_setup(l);
+  // byte offset of tap (0, 0)'s plane word, and that tap's input row and column
+  uint32_t xoff[XS];
+  int xiy[XS], xix[XS];
+  auto place = [&](int i, int* n) {  // position i of the tile -> tap (0, 0) and image
+    const int q = p0 + i < p.P ? p0 + i : 0;
+    const int ox = q % p.OW, t = q / p.OW, oy = t % p.OH;
+    *n = t / p.OH;
+    // a position past the end has no tap inside its image
+    return make_int2(p0 + i < p.P && i < T::kPos ? oy * p.stride - p.pad : -(1 << 30),
+                     ox * p.stride - p.pad);
+  };
+#pragma unroll
+  for (int i = 0; i < XS; ++i) {
+    int n;
+    const int2 e = place(4 * (wave + i * NW) + grp, &n);
+    xiy[i] = e.x;
+    xix[i] = e.y;
+    xoff[i] = ((uint32_t)((n * p.H + e.x) * p.W + e.y) * (uint32_t)(p.CG * NIN) + min(l, NIN - 1)) * 4u;
+  }
+  uint32_t mx = 0u, mw = 0u;         // largest magnitudes staged by this lane
+  uint32_t any = 0u, special = 0u;  // all its plane words; infinities and NaN among gathered codes
+
+  struct Chunk {
+    int ky, kx, cg, tap0, nc;
+  };
+  auto advance = [&](Chunk& c) {
+    c.tap0 += c.nc;
+    if constexpr (kFlat) {
+      c.nc = min(32, taps - c.tap0);
+    } else {
+      if (++c.cg == p.CG) {
+        c.cg = 0;
+        if (++c.kx == p.KW) {
+          c.kx = 0;
+          ++c.ky;
+        }
+      }
+      c.nc = min(32, p.C - 32 * c.cg);
+    }
+  };
+  auto inside = [&](int i, const Chunk& c) {
+    return (uint32_t)(xiy[i] + c.ky) < (uint32_t)p.H && (uint32_t)(xix[i] + c.kx) < (uint32_t)p.W;
+  };
+  auto word = [](const uint32_t* base, uint32_t byte) {
+    return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(base) + byte);
+  };
+  const uint32_t hi_step = (uint32_t)(min(l + 16, NIN - 1) - min(l, NIN - 1)) * 4u;
+  struct Raw {
+    uint32_t x[XS][kHigh ? 2 : 1], w[WS][kHigh ? 2 : 1];
+  };
+  auto fetch = [&](const Chunk& c, Raw& raw) {
+    if constexpr (!kFlat) {
+      const uint32_t d = (uint32_t)((c.ky * p.W + c.kx) * p.CG + c.cg) * (uint32_t)(4 * NIN);
+#pragma unroll
+      for (int i = 0; i < XS; ++i) {
+        const uint32_t o = inside(i, c) ? xoff[i] + d : 0u;
+        raw.x[i][0] = word(ifm, o);
+        if constexpr (kHigh) raw.x[i][1] = word(ifm, o + (inside(i, c) ? hi_step : 0u));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < WS; ++i) {
+      const int s = min(wave + i * NW, T::kWSets - 1);
+      const int t = 4 * (s & 7) + grp, mt = min(mt0 + (s >> 3), p.MT - 1);
+      const uint32_t o =
+          ((uint32_t)(c.tap0 + min(t, c.nc - 1)) * (uint32_t)p.MT + mt) * (uint32_t)(4 * NIN) +
+          (uint32_t)min(l, NIN - 1) * 4u;
+      raw.w[i][0] = word(w, o);
+      if constexpr (kHigh) raw.w[i][1] = word(w, o + hi_step);
+    }
+  };
+  // the codes of a flat chunk's IFM values, bit by bit: lane j is tap tap0 + j
+  auto gather = [&](const Chunk& c, int i) {
+    const int t = c.tap0 + min(j, c.nc - 1), s = t / p.C, ch = t - s * p.C;
+    int n;
+    const int2 e = place(i, &n);
+    const int iy = e.x + s / p.KW, ix = e.y + s % p.KW;
+    const bool ok = (uint32_t)iy < (uint32_t)p.H && (uint32_t)ix < (uint32_t)p.W && j < c.nc;
+    const uint32_t* src = ifm + (ok ? (uint32_t)((n * p.H + iy) * p.W + ix) * (uint32_t)NIN : 0u);
+    uint32_t q[NIN], code = 0u;
+    __builtin_memcpy(q, src, 4 * NIN);
+#pragma unroll
+    for (int b = 0; b < NIN; ++b) code |= __builtin_amdgcn_ubfe(q[b], ch, 1) << b;
+    special |= ok ? code >> (NIN - 1) : 0u;
+    return ok ? code : 0u;
+  };
+  auto stage = [&](const Chunk& c, Raw& raw, int buf, auto checked) {
+    constexpr bool kChecked = decltype(checked)::value;
+    auto put_x = [&](int i, uint32_t code) {
+      const uint32_t v = decode_scaled<A::wE, A::wI, A::kScaleX, kChecked>(code);
+      mx = max(mx, v & 0x7FFFFFFFu);
+      xs[buf][i][j] = __uint_as_float(v);
+    };
+    auto put_w = [&](int kern, int t, uint32_t code) {
+      const uint32_t v = decode_scaled<A::wE, A::wI, A::kScaleW, kChecked>(code);
+      mw = max(mw, v & 0x7FFFFFFFu);
+      ws[buf][kern][t ^ 2] = __uint_as_float(v);  // see the MAC
+    };
+    const uint32_t keep = c.nc < 32 ? (1u << c.nc) - 1u : ~0u;
+    // all of this wave's sets through the transpose together: its steps depend
+    // on each other, so one set alone would wait at each
+    constexpr int X = kFlat ? 0 : XS;
+    uint32_t P[X + WS], Q[X + WS];
+#pragma unroll
+    for (int i = 0; i < X; ++i) {
+      const bool ok = inside(i, c);
+      P[i] = ok && l < NIN ? raw.x[i][0] & keep : 0u;
+      Q[i] = 0u;
+      if constexpr (kHigh) Q[i] = ok && l + 16 < NIN ? raw.x[i][1] & keep : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < WS; ++i) {
+      const int t = 4 * ((wave + i * NW) & 7) + grp;
+      const uint32_t fill = l == A::wE + A::wI ? ~0u : 0u;  // -0
+      P[X + i] = t < c.nc ? (l < NIN ? raw.w[i][0] : 0u) : fill;
+      Q[X + i] = 0u;
+      if constexpr (kHigh) Q[X + i] = t < c.nc && l + 16 < NIN ? raw.w[i][1] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < X + WS; ++i) any |= kHigh ? Q[i] : P[i];
+    row_transpose(P, rt);
+    if constexpr (kHigh) row_transpose(Q, rt);
+#pragma unroll
+    for (int i = 0; i < X + WS; ++i) {  // the words of groups h and 2 + h
+      uint32_t a, b;
+      stage16_from_pairs(P[i], Q[i], a, b);
+      P[i] = a;
+      Q[i] = b;
+    }
+#pragma unroll
+    for (int i = 0; i < XS; ++i) {
+      const int s = wave + i * NW;
+      if (T::kXSets % NW != 0 && s >= T::kXSets) break;  // uniform
+      if constexpr (kFlat) {
+        put_x(4 * s + h, gather(c, 4 * s + h));
+        put_x(4 * s + 2 + h, gather(c, 4 * s + 2 + h));
+      } else {
+        put_x(4 * s + h, P[i]);
+        put_x(4 * s + 2 + h, Q[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < WS; ++i) {
+      const int s = wave + i * NW;
+      if (T::kWSets % NW != 0 && s >= T::kWSets) break;  // uniform
+      const int kern = (s >> 3) * 32 + j, t0 = 4 * (s & 7) + h;
+      put_w(kern, t0, P[X + i]);
+      put_w(kern, t0 + 2, Q[X + i]);
+    }
+  };
+
+  // All chunks in order; `four` takes the operands of four taps at a time, or
+  // with kChecked `one` those of a single tap (small code: it runs rarely).
+  auto run = [&](auto checked, auto&& four, auto&& one) {
+    constexpr bool kChecked = decltype(checked)::value;
+    // step ch computes chunk ch and stages chunk ch + 1; the first only stages
+    Chunk nx{0, 0, 0, 0, kFlat ? min(32, taps) : min(32, p.C)};
+    int nq = 0;  // groups of four taps of the chunk to compute
+    Raw raw;
+    for (int ch = -1; ch < nch; ++ch) {
+      const bool more = ch + 1 < nch;
+      if (more) fetch(nx, raw);
+      const lds_f32* xb = (const lds_f32*)&xs[ch & 1][(wp * 2 + h) * RP][0];
+      const lds_f32* wb = (const lds_f32*)&ws[ch & 1][wm * RM * 32 + j][0];
+      if constexpr (kChecked) {
+#pragma unroll 1
+        for (int t = 0; t < 4 * nq; ++t) {
+          float xv[RP], wv[RM];
+#pragma unroll
+          for (int r = 0; r < RP; ++r) xv[r] = xb[r * kRow + t];
+#pragma unroll
+          for (int m = 0; m < RM; ++m) wv[m] = wb[m * 32 * kRow + (t ^ 2)];
+          one(xv, wv);
+        }
+      } else if (nq > 0) {
+        auto load = [&](int q, f32x4(&xv)[RP], f32x4(&wv)[RM]) {
+#pragma unroll
+          for (int r = 0; r < RP; ++r) xv[r] = *(const lds_f32x4*)(xb + r * kRow + 4 * q);
+#pragma unroll
+          for (int m = 0; m < RM; ++m) wv[m] = *(const lds_f32x4*)(wb + m * 32 * kRow + 4 * q);
+        };
+        // operands of the next four taps are requested before this four's MACs
+        f32x4 xa[RP], wa[RM], xc[RP], wc[RM];
+        load(0, xa, wa);
+        int q = 0;
+        for (; q + 2 <= nq; q += 2) {
+          load(q + 1, xc, wc);
+          four(xa, wa);
+          load(q + 2 < nq ? q + 2 : q, xa, wa);
+          four(xc, wc);
+        }
+        if (q < nq) four(xa, wa);
+      }
+      if (more) stage(nx, raw, (ch + 1) & 1, checked);
+      nq = (nx.nc + 3) >> 2;
+      advance(nx);
+      __syncthreads();
+    }
+  };
+  auto nothing = [](const auto&, const auto&) {};
+
+  float out[RM][RP];
+  A::set_mode();
+  bool fits;
+  {
+    typename A::Acc acc[RM][RP];
+    float track = 0.0f;  // largest sum (kTrack)
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int r = 0; r < RP; ++r) acc[m][r] = 0;
+    run(std::false_type{}, [&](const f32x4(&xv)[RP], const f32x4(&wv)[RM]) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+#pragma unroll
+        for (int m = 0; m < RM; ++m) {
+          // weights lie two taps apart from the IFM values in their group of
+          // four, so that the two operands of a tap, each loaded four to an
+          // aligned register quad, come from different VGPR banks
+          const float wt = wv[m][t ^ 2], wk = A::prescale(wt);
+#pragma unroll
+          for (int r = 0; r < RP; ++r)
+            acc[m][r] = A::add(acc[m][r], A::product(wt, wk, xv[r][t]), track);
+        }
+      }
+    }, nothing);
+    // the largest operands of the workgroup's tile decide whether any product
+    // or sum can have left the format's range
+    atomicMax(&largest[0], mx);
+    atomicMax(&largest[1], mw);
+    if constexpr (A::kTrack) atomicMax(&largest[2], __float_as_uint(track));
+    if ((l == ((NIN - 1) & 15) && any != 0u) || special != 0u) largest[3] = 1u;
+    __syncthreads();
+    const float big = __uint_as_float(largest[0]) * pow2f(-A::kScaleX) *
+                      (__uint_as_float(largest[1]) * pow2f(-A::kScaleW));
+    fits = big < bound && largest[3] == 0u;
+    if constexpr (A::kTrack)
+      fits = fits && largest[2] < (uint32_t)(127 + A::kTop + A::kScale) << 23;
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int r = 0; r < RP; ++r) out[m][r] = A::value(acc[m][r]);
+  }
+  if (!fits) {  // uniform over the workgroup
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int r = 0; r < RP; ++r) out[m][r] = 0.0f;
+    run(std::true_type{}, nothing, [&](const float(&xv)[RP], const float(&wv)[RM]) {
+#pragma unroll
+      for (int m = 0; m < RM; ++m)
+#pragma unroll
+        for (int r = 0; r < RP; ++r) out[m][r] = A::mac_checked(out[m][r], wv[m], xv[r]);
+    });
+  }
+
+  // Epilogue: activation, conversion to the output format, store. Lane j of a
+  // half holds kernel 32 mt + j of a position: planes come out of the lane
+  // transpose, values and codes are stored 32 lanes side by side.
+#pragma unroll
+  for (int m = 0; m < RM; ++m) {
+    const int mt = mt0 + wm * RM + m;
+    uint32_t code[RP + (RP & 1)];
+#pragma unroll
+    for (int r = 0; r < RP + (RP & 1); ++r) {
+      const float v = r < RP ? out[m][r < RP ? r : 0] : 0.0f;
+      uint32_t b = __float_as_uint(v);
+      if constexpr (V::kAct != 0) b = (b & 0x80000000u) != 0u && v == v ? 0u : b;
+      code[r] = quantize_narrow(b, V::wE, V::wF_OUT);
+    }
+    if (p.ofm_kind == kOfmPlanes) {
+      lane_transpose(code, j);
+#pragma unroll
+      for (int r = 0; r < RP; ++r) {
+        const int pos = p0 + (wp * 2 + h) * RP + r;
+        if (pos < p.P && mt < p.MT && j < NOUT) ofm[((size_t)pos * p.MT + mt) * NOUT + j] = code[r];
+      }
+    } else {
+      const int kern = mt * 32 + j;
+#pragma unroll
+      for (int r = 0; r < RP; ++r) {
+        const int pos = p0 + (wp * 2 + h) * RP + r;
+        const uint32_t v = p.ofm_kind == kOfmF32 ? decode_narrow(code[r], V::wE, V::wF_OUT) : code[r];
+        if (pos < p.P && kern < p.M) ofm[(size_t)pos * p.M + kern] = v;
+      }
+    }
+  }
+}
+
+// Tile shapes (RM, RP, WP, WM) of the kernel, largest first; the choice among
+// them and the bitsliced kernels is made by value_plan (abi.hip).
+template <class V, int RM, int RP, int WP, int WM>
+hipError_t launch_value_tile(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
+                             const ConvParams& p, float bound, hipStream_t stream) {
+  using T = ValueTile<V, RM, RP, WP, WM>;
+  const dim3 grid((unsigned)((p.P + T::kPos - 1) / T::kPos),
+                  (unsigned)((p.MT + RM * WM - 1) / (RM * WM)));
+  if constexpr (T::kPos <= 32 && RM == 1) {
+    if (p.C < kFlatC) {
+      hipLaunchKernelGGL((conv2d_value_kernel<V, true, RM, RP, WP, WM>), grid, dim3(T::kThreads),
+                         0, stream, ifm, w, ofm, p, bound);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((conv2d_value_kernel<V, false, RM, RP, WP, WM>), grid, dim3(T::kThreads), 0,
+                     stream, ifm, w, ofm, p, bound);
+  return hipGetLastError();
+}
+
+template <class V>
+hipError_t launch_value(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm, const ConvParams& p,
+                        int tile, hipStream_t stream) {
+  using A = ValueMath<V>;
+  // The largest product of magnitudes, max|w| max|x|, for which neither a
+  // product nor a sum can reach 2^kTop: rounding is monotone, so the sums stay
+  // below those of T equal products P rounded up, which grow by P (1 + u) a
+  // tap, u half a unit in the last place, and stop growing at 2^(wF + 2) P,
+  // where P is less than half a unit of the sum. With kTrack the sums are
+  // looked at themselves.
+  const double u = ldexp(1.0, -(A::wA + 1)), taps = (double)p.KH * p.KW * p.C;
+  double grow = 1.0;
+  if (!A::kTrack) {
+    grow = taps * (A::kRtz ? 1.0 : exp(2.0 * taps * u));
+    const double stop = ldexp(1.0, A::wA + 2);
+    grow = grow < stop ? grow : stop;
+  }
+  const float bound = (float)(ldexp(1.0, A::kTop) * (1.0 - 4.0 * u) / grow);
+  switch (tile) {
+    case kTile112x64: return launch_value_tile<V, 1, 7, 8, 2>(ifm, w, ofm, p, bound, stream);
+    case kTile56x64: return launch_value_tile<V, 1, 7, 4, 2>(ifm, w, ofm, p, bound, stream);
+    case kTile32x64: return launch_value_tile<V, 2, 2, 8, 1>(ifm, w, ofm, p, bound, stream);
+    case kTile32x32: return launch_value_tile<V, 1, 2, 8, 1>(ifm, w, ofm, p, bound, stream);
+    case kTile16x32: return launch_value_tile<V, 1, 1, 8, 1>(ifm, w, ofm, p, bound, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace hobflops

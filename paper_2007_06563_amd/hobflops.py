@@ -50,7 +50,8 @@ class PackJob(ctypes.Structure):
 
 EXPORTS = ("hobflops_plane_words", "hobflops_pack", "hobflops_pack_batch", "hobflops_unpack",
            "hobflops_conv2d",
-           "hobflops_conv2d_supported", "hobflops_conv2d_algo", "hobflops_muladd", "hobflops_muladd_supported",
+           "hobflops_conv2d_supported", "hobflops_conv2d_algo", "hobflops_conv2d_value_ops",
+           "hobflops_muladd", "hobflops_muladd_supported",
            "hobflops_netlist_ops", "hobflops_avgpool", "hobflops_avgpool_supported",
            "hobflops_avgpool_netlist_ops", "hobflops_wait_failures", "hobflops_set_wait_limit",
            "hobflops_get_wait_limit", "hobflops_status_string")
@@ -72,6 +73,7 @@ def lib():
         L.hobflops_conv2d.argtypes = [vp, vp, vp, ctypes.POINTER(ConvDesc), vp]
         L.hobflops_conv2d_supported.argtypes = [ctypes.POINTER(ConvDesc)]
         L.hobflops_conv2d_algo.argtypes = [ctypes.POINTER(ConvDesc)]
+        L.hobflops_conv2d_value_ops.argtypes = [ctypes.POINTER(ConvDesc)]
         L.hobflops_muladd.argtypes = [vp, vp, vp, vp, i64, Fmt, Fmt, ci, vp]
         L.hobflops_muladd_supported.argtypes = [Fmt, Fmt, ci]
         L.hobflops_netlist_ops.argtypes = [Fmt, Fmt, ci] + [ctypes.POINTER(ci)] * 4
@@ -237,9 +239,19 @@ def conv2d_supported(d):
 
 
 def conv2d_algo(d):
-    """The kernel shape (ALGO_FUSED, ALGO_SPLIT or ALGO_SPLIT_COMPACT) conv2d
-    runs d in: d.algo, or what AUTO picks on the current device."""
+    """The bitsliced kernel shape (ALGO_FUSED, ALGO_SPLIT or ALGO_SPLIT_COMPACT)
+    of d: d.algo, or what AUTO picks on the current device unless it runs d on
+    float32 values (conv2d_value_ops)."""
     rc = lib().hobflops_conv2d_algo(ctypes.byref(d))
+    if rc < 0:
+        _check(rc)
+    return rc
+
+
+def conv2d_value_ops(d):
+    """Operations of one multiply-add where ALGO_AUTO runs d on float32 values, one
+    per lane, instead of bitsliced; else 0."""
+    rc = lib().hobflops_conv2d_value_ops(ctypes.byref(d))
     if rc < 0:
         _check(rc)
     return rc

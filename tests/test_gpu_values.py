@@ -1,0 +1,143 @@
+"""The convolution on float32 values (AUTO's other kernel) against the oracle,
+bit for bit: every product of two finite (5,3) values and every sum of two
+finite (4,3) values, in both roundings; and every generated variant at the edges
+of the kernel's tiles, chunks and formats.
+
+conv2d_value_ops says whether AUTO takes that kernel; every case here is one
+where it does.
+"""
+import numpy as np
+import pytest
+
+import oracle as orc
+from gpu_util import codes_of, dev, need_gpu, say
+from paper_2007_06563_amd import inputs as I
+from paper_2007_06563_amd import variants
+
+pytestmark = pytest.mark.gpu
+
+ROUNDINGS = pytest.mark.parametrize("rnd", [0, 1], ids=["rne", "rtz"])
+
+
+def conv_on_values(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, rnd, kind=None):
+    """AUTO's convolution of code tensors (NHWC / HWIO), which must run on values
+    -> output codes [N, OH, OW, M] (kind OFM_F32: float32 bits)."""
+    N, H, W, C = qi.shape
+    KH, KW, _, M = qw.shape
+    kind = hf.OFM_PLANES if kind is None else kind
+    d = hf.conv_desc(N, H, W, C, M, KH, KW, stride, pad, (wE, wi), (wE, wa), (wE, wo), act,
+                     hf.ALGO_AUTO, round=rnd, ofm_kind=kind)
+    assert hf.conv2d_value_ops(d) > 0, "AUTO does not run this case on values"
+    OH, OW = hf.conv_out_hw(d)
+    pi = hf.pack(dev(qi.astype(np.uint32).view(np.int32).reshape(-1, C)), (wE, wi))
+    pw = hf.pack(dev(qw.astype(np.uint32).view(np.int32).reshape(-1, M)), (wE, wi))
+    out = hf.conv2d(pi, pw, d)
+    if kind == hf.OFM_PLANES:
+        out = hf.unpack(out, N * OH * OW, M, (wE, wo), kind="code")
+    return codes_of(out).reshape(N, OH, OW, M)
+
+
+def finite_codes(wE, wF):
+    """Every canonical finite code: both zeros and every normal number."""
+    f = np.arange(1 << (wE + wF + 1), dtype=np.uint64)
+    s = f >> np.uint64(wE + wF) << np.uint64(wE + wF)
+    normal = f | np.uint64(1 << (wE + wF + 1))
+    return np.concatenate([np.unique(s), normal])
+
+
+@ROUNDINGS
+def test_every_product_of_finite_values(rnd):
+    """Each position holds one (5,3) value in one channel and +0 in the others, each
+    kernel the same (5,3) value in all channels: every output is one product."""
+    hf = need_gpu()
+    C = 1024
+    codes = finite_codes(5, 3)
+    for part in np.array_split(codes, 2):
+        x = np.zeros((1, 1, part.size, C), np.uint64)
+        x[0, 0, np.arange(part.size), (np.arange(part.size) * 37) % C] = part
+        w = np.broadcast_to(codes, (1, 1, C, codes.size))
+        say(f"conv on values, every product (5,3) rnd={rnd} positions={part.size}")
+        got = conv_on_values(hf, x, w, 1, 0, 5, 3, 4, 4, 0, rnd)
+        want = orc.conv2d(part.reshape(1, 1, -1, 1), codes.reshape(1, 1, 1, -1), 1, 0, 5, 3, 4, 4,
+                          rnd=rnd)
+        bad = np.argwhere(got != want)
+        assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
+
+
+@ROUNDINGS
+def test_every_sum_of_finite_values(rnd):
+    """Each position holds two (4,3) values in two channels, +0 in the others, the
+    kernel is 1 everywhere: every output is the sum of two values (products by
+    1 are exact), zeros and their signs included."""
+    hf = need_gpu()
+    C = 64
+    codes = finite_codes(4, 3)
+    a, b = (v.reshape(-1) for v in np.meshgrid(codes, codes, indexing="ij"))
+    one = np.uint64((1 << 8) | (7 << 3))  # exception 01, E = bias, F = 0
+    for lo in range(0, a.size, 8192):
+        n = min(8192, a.size - lo)
+        x = np.zeros((1, 1, n, C), np.uint64)
+        x[0, 0, :, 5], x[0, 0, :, 40] = a[lo:lo + n], b[lo:lo + n]
+        # the zeros between and after: -0 where every value so far may be -0
+        x[0, 0, :, :5] = x[0, 0, :, 41:] = np.uint64(1 << 7)
+        w = np.full((1, 1, C, 1), one)
+        say(f"conv on values, every sum (4,3) rnd={rnd} pairs {lo}..{lo + n}")
+        got = conv_on_values(hf, x, w, 1, 0, 4, 3, 4, 4, 0, rnd)
+        want = orc.conv2d(x, w, 1, 0, 4, 3, 4, 4, rnd=rnd)
+        bad = np.argwhere(got != want)
+        assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
+
+
+# (N, H, W, C, M, K, stride, pad): one position and one kernel; 3 and 15 channels
+# (chunks across pixels); 16, 31, 33 channels; tiles of 16, 32, 56 and 112
+# positions with one position more or less; one, two and three words of kernels
+# with one kernel more or less; a stride, no padding, wide padding.
+EDGES = [(1, 1, 1, 200, 1, 1, 1, 0), (1, 5, 3, 3, 33, 3, 1, 1), (2, 4, 4, 15, 31, 3, 2, 1),
+         (1, 4, 4, 16, 32, 3, 1, 1), (1, 3, 11, 31, 65, 3, 1, 1), (1, 7, 8, 33, 64, 3, 1, 1),
+         (2, 9, 9, 64, 40, 3, 2, 0), (1, 5, 7, 37, 96, 5, 1, 4)]
+
+
+@pytest.mark.parametrize("v", variants.CONV_VARIANTS, ids=variants.conv_tag)
+def test_every_variant_at_the_edges(v):
+    """Ordinary values; values around both ends of the range (products that
+    underflow, sums that cancel below the smallest normal number, overflow to
+    infinity); 2 % specials."""
+    hf = need_gpu()
+    wE, wi, wa, wo, act, rnd = v
+    g = np.random.default_rng([17, wE, wi, wa, wo, act, rnd])
+    top = 2.0 ** (2 ** (wE - 1))
+    for n, s in enumerate(EDGES):
+        N, H, W, C, M, K, stride, pad = s
+        for scale, specials in ((1.0, 0.0), (2.0 ** -((2 ** (wE - 1)) // 2), 0.0),
+                                (top ** 0.5, 0.0), (1.0, 0.02)):
+            ifm = (g.standard_normal((N, H, W, C)) * scale).astype(np.float32)
+            ifm[g.random(ifm.shape) < 0.3] = 0.0
+            w = (g.standard_normal((K, K, C, M)) * scale * 0.2).astype(np.float32)
+            if specials:
+                ifm, w = (I.inject_specials(t, g, specials) for t in (ifm, w))
+            qi, qw = orc.quantize_f32(ifm, wE, wi), orc.quantize_f32(w, wE, wi)
+            kind = (hf.OFM_PLANES, hf.OFM_CODE, hf.OFM_F32)[n % 3]
+            say(f"conv on values {variants.conv_tag(v)} {s} scale={scale} specials={specials}")
+            got = conv_on_values(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, rnd, kind)
+            want = orc.conv2d(qi, qw, stride, pad, wE, wi, wa, wo, act, rnd=rnd)
+            if kind == hf.OFM_F32:
+                want = orc.decode_f32(want, wE, wo).view(np.uint32).astype(np.uint64)
+            bad = np.argwhere(got != want)
+            assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
+
+
+def test_large_tiles():
+    """The 112x64 and 56x64 tiles (wide layers), ragged at both ends."""
+    hf = need_gpu()
+    for N, H, W, C, M in ((3, 47, 50, 64, 192), (2, 29, 31, 96, 250)):
+        g = np.random.default_rng([18, C])
+        ifm = np.maximum(g.standard_normal((N, H, W, C)), 0).astype(np.float32)
+        w = (g.standard_normal((3, 3, C, M)) * 0.05).astype(np.float32)
+        qi, qw = orc.quantize_f32(ifm, 5, 10), orc.quantize_f32(w, 5, 10)
+        say(f"conv on values, large tiles {N}x{H}x{W}x{C} -> {M}")
+        got = conv_on_values(hf, qi, qw, 1, 1, 5, 10, 11, 11, 0, 0)
+        pts = np.stack([g.integers(0, q, 8192) for q in got.shape], 1).astype(np.int64)
+        pts[:64, 2], pts[64:128, 1], pts[128:192, 3] = W - 1, H - 1, M - 1
+        want = orc.conv2d_points(qi, qw, pts, 1, 1, 5, 10, 11, 11)
+        bad = np.flatnonzero(got[pts[:, 0], pts[:, 1], pts[:, 2], pts[:, 3]] != want)
+        assert bad.size == 0, f"{bad.size} mismatches; first at {pts[bad[0]]}"
