@@ -382,7 +382,7 @@ def value_ops(wi, wa, rnd):
     if rnd == variants.RTZ:
         return 3 if exact else 4
     if wa > 10:
-        return 11 if exact else 14
+        return 13 if exact else 16
     lift = not exact and 23 - wa < 15
     return 5 if exact else 8 if lift else 7
 

@@ -31,7 +31,8 @@
 //    zero of their sign: the rounded product r is produced by a subtraction
 //    whose exact result it is, so it is flushed after rounding as the format
 //    asks, and a sum below the smallest normal number is always exact, so
-//    flushing it before rounding is the same.
+//    flushing it before rounding is the same. Of float64's operations only
+//    products are flushed, so there the sum passes through one.
 //  - Zero signs are IEEE's in every step.
 //  - Overflow and inputs that are infinite or NaN do not fit this: a workgroup
 //    that meets such an input, or whose inputs are so large that a sum could
@@ -108,7 +109,8 @@ struct ValueMath {
   // that 2^-1022 is the format's smallest normal number
   static __device__ __forceinline__ Acc add(Acc acc, float r, float& track) {
     if constexpr (kWide) {
-      const double s = __builtin_fma((double)r, 0x1p-896, acc);
+      // float64 additions keep numbers below 2^-1022, the multiplication does not
+      const double s = __builtin_fma(acc, 0x1p896, (double)r) * 0x1p-896;
       const double u = s * (double)((1LL << (52 - wA)) + 1);
       const double v = u - s;
       return u - v;
@@ -334,6 +336,7 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
 #pragma unroll
     for (int i = 0; i < WS; ++i) {
       const int t = 4 * ((wave + i * NW) & 7) + grp;
+      static_assert(A::wE + A::wI < 16);
       const uint32_t fill = l == A::wE + A::wI ? ~0u : 0u;  // -0
       P[X + i] = t < c.nc ? (l < NIN ? raw.w[i][0] : 0u) : fill;
       Q[X + i] = 0u;

@@ -88,6 +88,32 @@ def test_every_sum_of_finite_values(rnd):
         assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
 
 
+@pytest.mark.parametrize("v", variants.CONV_VARIANTS, ids=variants.conv_tag)
+def test_sums_around_the_smallest_normal_number(v):
+    """Two values of the lowest binades that nearly cancel, the last two taps of
+    each output: sums below the smallest normal number go to a zero of their
+    sign, then take part in one more sum."""
+    hf = need_gpu()
+    wE, wi, wa, wo, act, rnd = v
+    g = np.random.default_rng([29, wE, wi, wa, wo, act, rnd])
+    n, C, top = 2048, 64, np.uint64(1 << (wE + wi + 1))
+    one = top | np.uint64(((1 << (wE - 1)) - 1) << wi)
+    a = top | g.integers(0, 4 << wi, n, dtype=np.uint64)
+    b = top | np.maximum((a - top).astype(np.int64) + g.integers(-3, 4, n), 0).astype(np.uint64)
+    sign = g.integers(0, 2, n, dtype=np.uint64) << np.uint64(wE + wi)
+    x = np.zeros((1, 1, n, C), np.uint64)
+    x[0, 0, :, C - 3] = a ^ sign
+    x[0, 0, :, C - 2] = b ^ sign ^ np.uint64(1 << (wE + wi))
+    x[0, 0, :, C - 1] = np.where(g.random(n) < 0.5, np.uint64(1 << (wE + wi)),
+                                 top | g.integers(0, 2 << wi, n, dtype=np.uint64))
+    w = np.full((1, 1, C, 1), one)
+    say(f"conv on values, small sums {variants.conv_tag(v)}")
+    got = conv_on_values(hf, x, w, 1, 0, wE, wi, wa, wo, act, rnd)
+    want = orc.conv2d(x, w, 1, 0, wE, wi, wa, wo, act, rnd=rnd)
+    bad = np.argwhere(got != want)
+    assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
+
+
 # (N, H, W, C, M, K, stride, pad): one position and one kernel; 3 and 15 channels
 # (chunks across pixels); 16, 31, 33 channels; tiles of 16, 32, 56 and 112
 # positions with one position more or less; one, two and three words of kernels
