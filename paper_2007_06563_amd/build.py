@@ -567,12 +567,14 @@ hipError_t launch_muladd_{tag}(const uint32_t* a, const uint32_t* b, const uint3
         src = f"""// Generated: global average pooling variant {tag}. Do not edit.
 #include "kernels.hpp"
 #include "registry.hpp"
+#include "value.hpp"
 namespace hobflops {{
 namespace pool_{tag} {{
 {cache[accum]['text']}
 {cache[scale]['text']}
 struct V {{
   static constexpr int NIN = {nb(wE, wi)}, NACC = {nb(wE, wa)}, NOUT = {nb(wE, wo)};
+  static constexpr int wE = {wE}, wF_IN = {wi}, wF_ACC = {wa}, wF_OUT = {wo}, kRound = {rnd};
   static __device__ __forceinline__ void add(uint32_t (&acc)[NACC], const uint32_t (&x)[NACC]) {{
     {accum}(acc, x);
   }}
@@ -585,6 +587,11 @@ struct V {{
 hipError_t launch_pool_{tag}(const uint32_t* in, uint32_t* out, const PoolParams& p,
                               hipStream_t stream) {{
   const int64_t lanes = (int64_t)p.N * p.CG;
+  if (lanes <= kPoolValueGroups) {{
+    hipLaunchKernelGGL(avgpool_value_kernel<pool_{tag}::V>, dim3((unsigned)((lanes + 7) / 8)), dim3(256),
+                       0, stream, in, out, p, ValueMath<pool_{tag}::V>::bound((double)p.HW));
+    return hipGetLastError();
+  }}
   hipLaunchKernelGGL(avgpool_kernel<pool_{tag}::V>, dim3((unsigned)((lanes + 255) / 256)), dim3(256),
                      0, stream, in, out, p);
   return hipGetLastError();

@@ -131,6 +131,11 @@ constexpr int kAlgoAuto = 0, kAlgoFused = 1, kAlgoSplit = 2, kAlgoSplitCompact =
 // faster one: kAlgoValue + tile, a tile of positions x kernels a workgroup.
 constexpr int kAlgoValue = 4;
 constexpr int kTile112x64 = 0, kTile56x64 = 1, kTile32x64 = 2, kTile32x32 = 3, kTile16x32 = 4;
+// Pooling takes its kernel on values up to this many (image, channel word)
+// groups: there both take 2.15 clocks of a SIMD per instruction at two or more
+// waves each, and the bitsliced kernel's chain of 4.4 clocks an instruction lasts
+// as long as about 14 waves a SIMD of the other.
+constexpr int64_t kPoolValueGroups = 16384;
 constexpr int kFlatC = 16;  // fewer channels than this: chunks of taps across pixels
 
 

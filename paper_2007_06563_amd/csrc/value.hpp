@@ -84,9 +84,9 @@ struct ValueMath {
   // largest operands, so the largest sum is tracked (half an instruction a MAC).
   static constexpr bool kTrack = wE < 5 && wA + 5 > kTop;
 
-  // MODE: float32 rounding nearest or toward zero; float32 and float64 results
-  // below the smallest normal number flushed, such operands read as they are
-  // (bits 5:4 and 7:6 = 1).
+  // MODE: float32 rounding nearest or toward zero; float32 results and float64
+  // products below the smallest normal number flushed, such operands read as
+  // they are (bits 5:4 and 7:6 = 1).
   static __device__ __forceinline__ void set_mode() {
     __builtin_amdgcn_s_setreg(1 | (0 << 6) | (7 << 11), 0x50 | (kRtz ? 3 : 0));
   }
@@ -142,8 +142,7 @@ struct ValueMath {
     if constexpr (!kRtz) b += ((b >> k) & 1u) + ((1u << (k - 1)) - 1u);
     return range(__uint_as_float((b & kMask) | (v != v ? 0x7FC00000u : 0u)));
   }
-  static __device__ __forceinline__ float mac_checked(float acc, float w, float x) {
-    const float r = round_checked((w * pow2f(-kScaleX - kScaleW)) * x);
+  static __device__ __forceinline__ float add_checked(float acc, float r) {
     if constexpr (kWide) {
       const double s = (double)acc + (double)r;
       const double u = s * (double)((1LL << (52 - wA)) + 1);
@@ -152,6 +151,25 @@ struct ValueMath {
     } else {
       return round_checked(acc + r);
     }
+  }
+  static __device__ __forceinline__ float mac_checked(float acc, float w, float x) {
+    return add_checked(acc, round_checked((w * pow2f(-kScaleX - kScaleW)) * x));
+  }
+  // The largest magnitude of an operand (a product of operands) for which no
+  // sum of `taps` of them can reach 2^kTop: rounding is monotone, so the sums
+  // stay below those of `taps` equal terms P rounded up, which grow by P (1 + u)
+  // a tap, u half a unit in the last place, and stop growing at 2^(wF + 2) P,
+  // where P is less than half a unit of the sum. With kTrack the sums are
+  // looked at themselves.
+  static float bound(double taps) {
+    const double u = ldexp(1.0, -(wA + 1));
+    double grow = 1.0;
+    if (!kTrack) {
+      grow = taps * (kRtz ? 1.0 : exp(2.0 * taps * u));
+      const double stop = ldexp(1.0, wA + 2);
+      grow = grow < stop ? grow : stop;
+    }
+    return (float)(ldexp(1.0, kTop) * (1.0 - 4.0 * u) / grow);
   }
 };
 
@@ -514,6 +532,87 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
   }
 }
 
+// Global average pooling on values, for few (image, channel word) groups: the
+// bitsliced kernel gives a group to a lane, whose chain of H W adds of some 130
+// instructions then sets the time (16x7x7x1024, (5,4): 256 such lanes, 15.4 us).
+// Here a half wave takes a group, a lane a channel: a set (see the convolution)
+// is two positions of the wave's two groups, its words are loaded kAhead sets
+// together, and each value is added in four operations. About 10 instructions
+// per group and position instead of 2, so the bitsliced kernel keeps launches of
+// many groups (launch_pool).
+template <class V>
+__global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __restrict__ in,
+                                                            uint32_t* __restrict__ out,
+                                                            PoolParams p, float bound) {
+  using A = ValueMath<V>;
+  constexpr int NIN = V::NIN, NOUT = V::NOUT, kAhead = 8, kSign = V::wE + V::wF_IN;
+  constexpr bool kHigh = NIN > 16;
+  const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5;
+  const int row = lane >> 4, l = lane & 15;
+  const int64_t groups = (int64_t)p.N * p.CG;
+  const int64_t first = 2 * ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (first >= groups) return;  // uniform over the wave
+  // row r of a set: group first + (r >> 1), position (r & 1) of the two
+  const int64_t q = first + (row >> 1) < groups ? first + (row >> 1) : groups - 1;
+  const int64_t n = q / p.CG, cg = q - n * p.CG;
+  const uint32_t* src = in + ((size_t)n * p.HW * p.CG + cg) * NIN;
+  const size_t step = (size_t)p.CG * NIN;
+  const int lo = min(l, NIN - 1), hi = min(l + 16, NIN - 1);
+  const RowT rt = row_transpose_setup(l);
+  uint32_t mx = 0u, any = 0u;
+  // add(x) for every position in order
+  auto walk = [&](auto checked, auto&& add) {
+    constexpr bool kChecked = decltype(checked)::value;
+    for (int s0 = 0; 2 * s0 < p.HW; s0 += kAhead) {
+      uint32_t P[kAhead], Q[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const uint32_t* at = src + (size_t)min(2 * (s0 + k) + (row & 1), p.HW - 1) * step;
+        P[k] = at[lo];
+        Q[k] = kHigh ? at[hi] : 0u;
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const bool have = 2 * (s0 + k) + (row & 1) < p.HW;
+        // past the end: -0, which changes no sum
+        P[k] = have ? (l < NIN ? P[k] : 0u) : (l == kSign ? ~0u : 0u);
+        if constexpr (kHigh) Q[k] = have ? (l + 16 < NIN ? Q[k] : 0u) : (l + 16 == kSign ? ~0u : 0u);
+        any |= kHigh ? Q[k] : P[k];
+      }
+      row_transpose(P, rt);
+      if constexpr (kHigh) row_transpose(Q, rt);
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        uint32_t a, b;
+        stage16_from_pairs(P[k], Q[k], a, b);
+        const uint32_t va = decode_scaled<V::wE, V::wF_IN, kChecked ? 0 : A::kScale, kChecked>(a);
+        const uint32_t vb = decode_scaled<V::wE, V::wF_IN, kChecked ? 0 : A::kScale, kChecked>(b);
+        mx = max(mx, max(va & 0x7FFFFFFFu, vb & 0x7FFFFFFFu));
+        add(__uint_as_float(va));
+        add(__uint_as_float(vb));
+      }
+    }
+  };
+  A::set_mode();
+  typename A::Acc acc = 0;
+  float track = 0.0f;
+  walk(std::false_type{}, [&](float x) { acc = A::add(acc, x, track); });
+  float v = A::value(acc);
+  const bool bad = !(__uint_as_float(mx) * pow2f(-A::kScale) < bound) ||
+                   (l == ((NIN - 1) & 15) && any != 0u) ||
+                   (A::kTrack && __float_as_uint(track) >= (uint32_t)(127 + A::kTop + A::kScale) << 23);
+  if (__any(bad)) {  // infinities, NaN, or sums that may leave the range
+    v = 0.0f;
+    walk(std::true_type{}, [&](float x) { v = A::add_checked(v, x); });
+  }
+  // the product of two accumulator values is exact in float32
+  const float scale =
+      __uint_as_float(decode_scaled<V::wE, V::wF_ACC, 0, true>(p.scale));
+  uint32_t code[2] = {quantize_narrow(__float_as_uint(v * scale), V::wE, V::wF_OUT), 0u};
+  lane_transpose(code, j);
+  if (first + h < groups && j < NOUT) out[(size_t)(first + h) * NOUT + j] = code[0];
+}
+
 // Tile shapes (RM, RP, WP, WM) of the kernel, largest first; the choice among
 // them and the bitsliced kernels is made by value_plan (abi.hip).
 template <class V, int RM, int RP, int WP, int WM>
@@ -537,21 +636,7 @@ hipError_t launch_value_tile(const uint32_t* ifm, const uint32_t* w, uint32_t* o
 template <class V>
 hipError_t launch_value(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm, const ConvParams& p,
                         int tile, hipStream_t stream) {
-  using A = ValueMath<V>;
-  // The largest product of magnitudes, max|w| max|x|, for which neither a
-  // product nor a sum can reach 2^kTop: rounding is monotone, so the sums stay
-  // below those of T equal products P rounded up, which grow by P (1 + u) a
-  // tap, u half a unit in the last place, and stop growing at 2^(wF + 2) P,
-  // where P is less than half a unit of the sum. With kTrack the sums are
-  // looked at themselves.
-  const double u = ldexp(1.0, -(A::wA + 1)), taps = (double)p.KH * p.KW * p.C;
-  double grow = 1.0;
-  if (!A::kTrack) {
-    grow = taps * (A::kRtz ? 1.0 : exp(2.0 * taps * u));
-    const double stop = ldexp(1.0, A::wA + 2);
-    grow = grow < stop ? grow : stop;
-  }
-  const float bound = (float)(ldexp(1.0, A::kTop) * (1.0 - 4.0 * u) / grow);
+  const float bound = ValueMath<V>::bound((double)p.KH * p.KW * p.C);
   switch (tile) {
     case kTile112x64: return launch_value_tile<V, 1, 7, 8, 2>(ifm, w, ofm, p, bound, stream);
     case kTile56x64: return launch_value_tile<V, 1, 7, 4, 2>(ifm, w, ofm, p, bound, stream);

@@ -89,6 +89,33 @@ def test_avgpool_edge_shapes(shape):
     assert np.array_equal(got, orc.avgpool(x, 5, 4, 5, 4))
 
 
+@pytest.mark.parametrize("rnd", [variants.RNE, variants.RTZ], ids=["rne", "rtz"])
+@pytest.mark.parametrize("groups", [16384, 16385])
+def test_avgpool_both_kernels(groups, rnd):
+    """The last group count of the kernel on values and the first of the
+    bitsliced one, an odd map."""
+    hf = need_gpu()
+    x = pool_inputs(groups, groups, 1, 3, 20, 5, 4, specials=0.01)
+    say(f"avgpool {groups} groups rnd={rnd}")
+    got = run_pool(hf, x, 5, 4, 4, 4, rnd)
+    assert np.array_equal(got, orc.avgpool(x, 5, 4, 4, 4, rnd=rnd))
+
+
+@pytest.mark.parametrize("v", variants.POOL_VARIANTS, ids=variants.pool_tag)
+def test_avgpool_ends_of_the_range(v):
+    """Sums that overflow, and sums that cancel below the smallest normal number;
+    an odd number of groups and of positions."""
+    hf = need_gpu()
+    wE, wi, wa, wo, rnd = v
+    g = np.random.default_rng([19, wE, wi, wa, rnd])
+    for scale in (2.0 ** (2 ** (wE - 1) - 1), 2.0 ** -(2 ** (wE - 1) - 3)):
+        x = (g.standard_normal((3, 5, 5, 20)) * scale).astype(np.float32)
+        codes = orc.quantize_f32(x, wE, wi)
+        say(f"avgpool {variants.pool_tag(v)} scale={scale}")
+        got = run_pool(hf, codes, wE, wi, wa, wo, rnd)
+        assert np.array_equal(got, orc.avgpool(codes, wE, wi, wa, wo, rnd=rnd)), scale
+
+
 def test_avgpool_of_a_conv_output():
     """Conv (planes stay on the GPU) then pooling, as at the end of a network."""
     hf = need_gpu()
