@@ -132,10 +132,11 @@ constexpr int kAlgoAuto = 0, kAlgoFused = 1, kAlgoSplit = 2, kAlgoSplitCompact =
 constexpr int kAlgoValue = 4;
 constexpr int kTile112x64 = 0, kTile56x64 = 1, kTile32x64 = 2, kTile32x32 = 3, kTile16x32 = 4;
 // Pooling takes its kernel on values up to this many (image, channel word)
-// groups: there both take 2.15 clocks of a SIMD per instruction at two or more
-// waves each, and the bitsliced kernel's chain of 4.4 clocks an instruction lasts
-// as long as about 14 waves a SIMD of the other.
-constexpr int64_t kPoolValueGroups = 16384;
+// groups: its time grows with them, the bitsliced kernel's is that of one lane's
+// chain up to some 32,000. Maps of 7x7, on values / bitsliced: (5,3) 4096 groups
+// 8.6 / 13.9 us, 8192 14.5 / 14.0; (5,11) 11.0 / 29.4 and 19.1 / 29.6; other
+// formats lie between, and longer maps favour it more.
+constexpr int64_t kPoolValueGroups = 6144;
 constexpr int kFlatC = 16;  // fewer channels than this: chunks of taps across pixels
 
 

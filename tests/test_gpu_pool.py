@@ -90,7 +90,7 @@ def test_avgpool_edge_shapes(shape):
 
 
 @pytest.mark.parametrize("rnd", [variants.RNE, variants.RTZ], ids=["rne", "rtz"])
-@pytest.mark.parametrize("groups", [16384, 16385])
+@pytest.mark.parametrize("groups", [6144, 6145])
 def test_avgpool_both_kernels(groups, rnd):
     """The last group count of the kernel on values and the first of the
     bitsliced one, an odd map."""
