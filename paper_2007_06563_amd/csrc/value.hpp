@@ -258,7 +258,9 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
     const int2 e = place(4 * (wave + i * NW) + grp, &n);
     xiy[i] = e.x;
     xix[i] = e.y;
-    xoff[i] = ((uint32_t)((n * p.H + e.x) * p.W + e.y) * (uint32_t)(p.CG * NIN) + min(l, NIN - 1)) * 4u;
+    // modulo 2^32 (positions past the end and taps above the image are never read)
+    const uint32_t at = (uint32_t)(n * p.H + e.x) * (uint32_t)p.W + (uint32_t)e.y;
+    xoff[i] = (at * (uint32_t)(p.CG * NIN) + min(l, NIN - 1)) * 4u;
   }
   uint32_t mx = 0u, mw = 0u;         // largest magnitudes staged by this lane
   uint32_t any = 0u, special = 0u;  // all its plane words; infinities and NaN among gathered codes
