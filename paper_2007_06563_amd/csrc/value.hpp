@@ -83,6 +83,12 @@ struct ValueMath {
   // up to 2^3 leaves the range): no useful bound of the sums follows from the
   // largest operands, so the largest sum is tracked (half an instruction a MAC).
   static constexpr bool kTrack = wE < 5 && wA + 5 > kTop;
+  static_assert(!(kTrack && kWide), "float64 sums are not tracked");
+  // The bits of the smallest sum out of range before its rounding, scaled: to
+  // nearest, half a unit in the last place below 2^kTop rounds up to it (a tie goes
+  // to 2^kTop, whose last place is even).
+  static constexpr uint32_t kOverflow =
+      ((uint32_t)(127 + kTop + kScale) << 23) - (kRtz ? 0u : 1u << (k - 1));
 
   // MODE: float32 rounding nearest or toward zero; float32 results and float64
   // products below the smallest normal number flushed, such operands read as
@@ -481,7 +487,7 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
                       (__uint_as_float(largest[1]) * pow2f(-A::kScaleW));
     fits = big < bound && largest[3] == 0u;
     if constexpr (A::kTrack)
-      fits = fits && largest[2] < (uint32_t)(127 + A::kTop + A::kScale) << 23;
+      fits = fits && largest[2] < A::kOverflow;
 #pragma unroll
     for (int m = 0; m < RM; ++m)
 #pragma unroll
@@ -602,7 +608,7 @@ __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __re
   float v = A::value(acc);
   const bool bad = !(__uint_as_float(mx) * pow2f(-A::kScale) < bound) ||
                    (l == ((NIN - 1) & 15) && any != 0u) ||
-                   (A::kTrack && __float_as_uint(track) >= (uint32_t)(127 + A::kTop + A::kScale) << 23);
+                   (A::kTrack && __float_as_uint(track) >= A::kOverflow);
   if (__any(bad)) {  // infinities, NaN, or sums that may leave the range
     v = 0.0f;
     walk(std::true_type{}, [&](float x) { v = A::add_checked(v, x); });

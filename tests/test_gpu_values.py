@@ -114,6 +114,44 @@ def test_sums_around_the_smallest_normal_number(v):
     assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
 
 
+def climbs(wE, wi, wa):
+    """Chains of finite values whose sums reach the accumulator's largest number
+    and then take one more term of about half a unit in its last place, before
+    they fall again: lists of (exponent, fraction, sign)."""
+    top = (1 << wE) - (1 << (wE - 1)) + 1  # 2^top is the first power of two out of range
+    full = (1 << wi) - 1
+    half = (top - 2 - wa, 0, 0)  # half a unit
+    for start in ([(top - 1, full, 0)], [(top - 2, full, 0)] * 2,
+                  [(top - 1 - i, 0, 0) for i in range(wi + 1)]):
+        up = start + [(top - 2 - wi - i, 0, 0) for i in range(wa - wi)]
+        for last in ([], [half], [(half[0] - 1, full, 0)], [(half[0], 1, 0)],
+                     [(half[0] - 1, 0, 0)] * 2, [(half[0] + 1, 0, 0)]):
+            for fall in ([], [(top - 2, 0, 1)], [(half[0] + 2, 0, 1)] * 2):
+                yield up + last + fall
+
+
+@pytest.mark.parametrize("v", variants.CONV_VARIANTS, ids=variants.conv_tag)
+def test_sums_around_the_largest_number(v):
+    """Sums that end on the largest finite number, or round up past it and fall
+    again (an infinity stays one), in both signs. A launch holds one chain, so that
+    no other one can make its tile take the range-checked route."""
+    hf = need_gpu()
+    wE, wi, wa, wo, act, rnd = v
+    bias, C = (1 << (wE - 1)) - 1, 70
+    one = np.uint64((1 << (wE + wi + 1)) | (bias << wi))
+    w = np.full((1, 1, C, 2), one)
+    w[..., 1] |= np.uint64(1 << (wE + wi))  # the same chain negated
+    say(f"conv on values, sums around the largest number {variants.conv_tag(v)}")
+    for n, chain in enumerate(climbs(wE, wi, wa)):
+        x = np.zeros((1, 1, 1, C), np.uint64)
+        at = 25 + np.arange(len(chain))  # across the end of the first channel word
+        x[0, 0, 0, at] = [(1 << (wE + wi + 1)) | (s << (wE + wi)) | (e + bias) << wi | f
+                          for e, f, s in chain]
+        got = conv_on_values(hf, x, w, 1, 0, wE, wi, wa, wo, act, rnd)
+        want = orc.conv2d(x, w, 1, 0, wE, wi, wa, wo, act, rnd=rnd)
+        assert np.array_equal(got, want), f"chain {n} {chain}: {got} instead of {want}"
+
+
 # (N, H, W, C, M, K, stride, pad): one position and one kernel; 3 and 15 channels
 # (chunks across pixels); 16, 31, 33 channels; tiles of 16, 32, 56 and 112
 # positions with one position more or less; one, two and three words of kernels
