@@ -48,6 +48,18 @@ struct PoolParams {
   uint32_t scale;
 };
 
+// The positions of a map of HW >= 1, in pairs: pair i holds positions 2i and
+// 2i + 1. Unsigned, as HW goes up to INT32_MAX and a walk in steps of several
+// pairs looks past the end.
+struct PoolPairs {
+  uint32_t HW;
+  __host__ __device__ bool more(uint32_t i) const { return 2u * i < HW; }
+  __host__ __device__ bool have(uint32_t i, uint32_t r) const { return 2u * i + r < HW; }
+  __host__ __device__ uint32_t at(uint32_t i, uint32_t r) const {  // the last one past the end
+    return have(i, r) ? 2u * i + r : HW - 1u;
+  }
+};
+
 // What the convolution writes (hobflops_conv_desc.ofm_kind): PL32 planes, or
 // per value, row-major [P][M], float32 values or uint32 codes.
 constexpr int kOfmPlanes = 0, kOfmF32 = 1, kOfmCode = 2;
@@ -668,10 +680,10 @@ __global__ __launch_bounds__(256) void avgpool_kernel(const uint32_t* __restrict
   constexpr int kAhead = 4;
   quad_t buf[kAhead][NQ];
   const size_t last = (size_t)(p.HW - 1) * step;
-  auto pos_ptr = [&](int i) { return src + min((size_t)i * step, last); };
+  auto pos_ptr = [&](uint32_t i) { return src + min((size_t)i * step, last); };
 #pragma unroll
   for (int k = 0; k < kAhead; ++k) load(buf[k], pos_ptr(k));
-  auto add_pos = [&](quad_t (&q)[NQ], int i) {
+  auto add_pos = [&](quad_t (&q)[NQ], uint32_t i) {
     // a scheduling barrier per position: the scheduler would otherwise hoist
     // parts of later adds (those on x alone), and their waits would take in
     // the loads requested ahead
@@ -684,14 +696,16 @@ __global__ __launch_bounds__(256) void avgpool_kernel(const uint32_t* __restrict
     V::add(acc, x);
     load(q, pos_ptr(i + kAhead));
   };
-  int i = 0;
-  for (; i + kAhead <= p.HW; i += kAhead) {
+  // unsigned positions, as above: those requested ahead lie past the end
+  const uint32_t HW = (uint32_t)p.HW;
+  uint32_t i = 0;
+  for (; i + kAhead <= HW; i += kAhead) {
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) add_pos(buf[k], i + k);
   }
 #pragma unroll
   for (int k = 0; k < kAhead - 1; ++k)
-    if (i + k < p.HW) add_pos(buf[k], i + k);
+    if (i + k < HW) add_pos(buf[k], i + k);
   uint32_t sp[NACC], r[NOUT];
 #pragma unroll
   for (int b = 0; b < NACC; ++b) sp[b] = ((p.scale >> b) & 1u) ? 0xFFFFFFFFu : 0u;

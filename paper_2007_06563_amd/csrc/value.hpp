@@ -567,21 +567,22 @@ __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __re
   const size_t step = (size_t)p.CG * NIN;
   const int lo = min(l, NIN - 1), hi = min(l + 16, NIN - 1);
   const RowT rt = row_transpose_setup(l);
+  const PoolPairs pairs{(uint32_t)p.HW};
   uint32_t mx = 0u, any = 0u;
   // add(x) for every position in order
   auto walk = [&](auto checked, auto&& add) {
     constexpr bool kChecked = decltype(checked)::value;
-    for (int s0 = 0; 2 * s0 < p.HW; s0 += kAhead) {
+    for (uint32_t s0 = 0; pairs.more(s0); s0 += kAhead) {
       uint32_t P[kAhead], Q[kAhead];
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
-        const uint32_t* at = src + (size_t)min(2 * (s0 + k) + (row & 1), p.HW - 1) * step;
+        const uint32_t* at = src + (size_t)pairs.at(s0 + k, row & 1) * step;
         P[k] = at[lo];
         Q[k] = kHigh ? at[hi] : 0u;
       }
 #pragma unroll
       for (int k = 0; k < kAhead; ++k) {
-        const bool have = 2 * (s0 + k) + (row & 1) < p.HW;
+        const bool have = pairs.have(s0 + k, row & 1);
         // past the end: -0, which changes no sum
         P[k] = have ? (l < NIN ? P[k] : 0u) : (l == kSign ? ~0u : 0u);
         if constexpr (kHigh) Q[k] = have ? (l + 16 < NIN ? Q[k] : 0u) : (l + 16 == kSign ? ~0u : 0u);
