@@ -301,7 +301,9 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
   };
   auto fetch = [&](const Chunk& c, Raw& raw) {
     if constexpr (!kFlat) {
-      const uint32_t d = (uint32_t)((c.ky * p.W + c.kx) * p.CG + c.cg) * (uint32_t)(4 * NIN);
+      // modulo 2^32: a tap row beside the image may lie far past it
+      const uint32_t d = (((uint32_t)c.ky * (uint32_t)p.W + (uint32_t)c.kx) * (uint32_t)p.CG +
+                          (uint32_t)c.cg) * (uint32_t)(4 * NIN);
 #pragma unroll
       for (int i = 0; i < XS; ++i) {
         const uint32_t o = inside(i, c) ? xoff[i] + d : 0u;
