@@ -254,7 +254,8 @@ static int resolve_algo(const hobflops_conv_desc* d, const ConvVariant* v, int* 
 //    more: the chip's share of the fused netlist at 1.73 ns an instruction
 //    (4x224x224x3 -> 64: 73 us).
 // The 16x32 and 32x32 tiles alone handle fewer than kFlatC channels. Byte
-// offsets in that kernel are 32 bits wide.
+// offsets in that kernel are 32 bits wide, and a launch has fewer than 2^32
+// threads along x, of which that kernel takes 9 to 32 a position.
 static int value_plan(const ConvParams& p, const ConvVariant& v, int algo, int cus) {
   const int64_t nin = 3 + v.wE + v.wF_in, taps = (int64_t)p.KH * p.KW * p.C;
   if ((int64_t)p.N * p.H * p.W * p.CG * nin >= (int64_t)1 << 29 ||
@@ -262,17 +263,19 @@ static int value_plan(const ConvParams& p, const ConvVariant& v, int algo, int c
     return -1;
   const double t = (double)taps;
   struct Tile {
-    int pos, mtiles, chains;
+    int pos, mtiles, chains, threads;
     double tap_ns, fixed_us;
   };
   static const Tile kTiles[] = {
-      {112, 2, 28, 0.0, 11.0}, {56, 2, 14, 10.0, 6.0}, {32, 2, 8, 13.0, 4.0},
-      {32, 1, 4, 18.0, 3.0},   {16, 1, 2, 20.0, 2.5}};
+      {112, 2, 28, 1024, 0.0, 11.0}, {56, 2, 14, 512, 10.0, 6.0}, {32, 2, 8, 512, 13.0, 4.0},
+      {32, 1, 4, 512, 18.0, 3.0},    {16, 1, 2, 512, 20.0, 2.5}};
   int best = -1;
   double best_us = 0.0;
   for (int k = p.C < kFlatC ? kTile32x32 : 0; k <= kTile16x32; ++k) {
     const Tile& q = kTiles[k];
-    const int64_t n = (((int64_t)p.P + q.pos - 1) / q.pos) * ((p.MT + q.mtiles - 1) / q.mtiles);
+    const int64_t nx = ((int64_t)p.P + q.pos - 1) / q.pos;
+    if (nx * q.threads > (int64_t)UINT32_MAX) continue;
+    const int64_t n = nx * ((p.MT + q.mtiles - 1) / q.mtiles);
     const double rounds = (double)((n + cus - 1) / cus);
     const double us = rounds * (t * (q.chains * 1.26 * v.value_ops + q.tap_ns) * 1e-3 + q.fixed_us);
     if (best < 0 || us < best_us) {
@@ -290,7 +293,7 @@ static int value_plan(const ConvParams& p, const ConvVariant& v, int algo, int c
   } else {
     tap_ns = v.accum_ops * 2.09 * (waves > simds ? 2.0 : 1.0);
   }
-  return best_us < t * tap_ns * 1e-3 + 4.0 ? best : -1;
+  return best >= 0 && best_us < t * tap_ns * 1e-3 + 4.0 ? best : -1;
 }
 
 // The kernel's parameters of a checked descriptor (those that come with the

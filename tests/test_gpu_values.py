@@ -205,3 +205,13 @@ def test_large_tiles():
         want = orc.conv2d_points(qi, qw, pts, 1, 1, 5, 10, 11, 11)
         bad = np.flatnonzero(got[pts[:, 0], pts[:, 1], pts[:, 2], pts[:, 3]] != want)
         assert bad.size == 0, f"{bad.size} mismatches; first at {pts[bad[0]]}"
+
+
+def test_launch_limit():
+    """A launch has fewer than 2^32 threads along x; AUTO runs layers of more on the
+    bitsliced kernel, which needs one a position. Nothing is launched here."""
+    hf = need_gpu()
+    for pad, on_values in ((10000, True), (11500, False)):  # 4.0e8 and 5.3e8 positions
+        d = hf.conv_desc(1, 1, 1, 64, 64, 1, 1, 1, pad, (5, 10), (5, 21), (5, 21), 0,
+                         hf.ALGO_AUTO, round=0)
+        assert (hf.conv2d_value_ops(d) > 0) == on_values, pad
