@@ -48,7 +48,8 @@
  *  - hobflops_netlist_ops reports the fused MAC, the multiplier, the
  *    accumulating adder and the element-wise MAC separately;
  *  - hobflops_pack_batch, hobflops_avgpool, hobflops_conv2d_algo,
- *    hobflops_conv2d_value_ops and the *_supported queries are additions.
+ *    hobflops_conv2d_value_ops, hobflops_conv2d_value_tile,
+ *    hobflops_conv2d_on_values and the *_supported queries are additions.
  */
 #ifndef HOBFLOPS_H
 #define HOBFLOPS_H
@@ -196,6 +197,29 @@ int hobflops_conv2d_algo(const hobflops_conv_desc* d);
  * (float64 ones counted twice) if so, 0 if it runs bitsliced or d->algo names
  * a shape, or a negative status as hobflops_conv2d_algo. Launches nothing. */
 int hobflops_conv2d_value_ops(const hobflops_conv_desc* d);
+
+/* Tiles of the kernel on float32 values: output positions x kernels of a
+ * workgroup. */
+enum {
+  HOBFLOPS_TILE_112X64 = 1,
+  HOBFLOPS_TILE_56X64 = 2,
+  HOBFLOPS_TILE_32X64 = 3,
+  HOBFLOPS_TILE_32X32 = 4,
+  HOBFLOPS_TILE_16X32 = 5
+};
+
+/* The tile (HOBFLOPS_TILE_*) AUTO runs d in on float32 values, 0 if it runs
+ * bitsliced or d->algo names a shape, or a negative status as
+ * hobflops_conv2d_algo. Launches nothing. */
+int hobflops_conv2d_value_tile(const hobflops_conv_desc* d);
+
+/* hobflops_conv2d on float32 values in the given tile, whichever kernel AUTO
+ * would pick (the results are the same bits; to measure and test the tiles).
+ * d->algo must be HOBFLOPS_ALGO_AUTO. HOBFLOPS_EUNSUPPORTED where the tile does
+ * not take d: fewer than 16 channels (but in the last two tiles), 2 GiB of
+ * input planes or weight planes, or 2^32 threads along the launch's x. */
+int hobflops_conv2d_on_values(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
+                              const hobflops_conv_desc* d, int tile, void* stream);
 
 /* Element-wise r = add(widen(c), mul(a, b)) over n elements of flat PL32
  * tensors (rows 1, len n): a, b, c in in_fmt, r in acc_fmt (same wE,

@@ -238,6 +238,26 @@ static int resolve_algo(const hobflops_conv_desc* d, const ConvVariant* v, int* 
   return HOBFLOPS_OK;
 }
 
+// Tiles of the kernel on float32 values: positions and 32-kernel words a
+// workgroup, its accumulator chains a SIMD and its threads.
+struct ValueTileShape {
+  int pos, mtiles, chains, threads;
+};
+static const ValueTileShape kValueTiles[] = {
+    {112, 2, 28, 1024}, {56, 2, 14, 512}, {32, 2, 8, 512}, {32, 1, 4, 512}, {16, 1, 2, 512}};
+
+// Whether that kernel takes the layer in tile k: the 16x32 and 32x32 tiles alone
+// handle fewer than kFlatC channels, byte offsets in it are 32 bits wide, and a
+// launch has fewer than 2^32 threads along x, of which it takes 9 to 32 a position.
+static bool value_tile_ok(const ConvParams& p, const ConvVariant& v, int k) {
+  const int64_t nin = 3 + v.wE + v.wF_in, taps = (int64_t)p.KH * p.KW * p.C;
+  const ValueTileShape& q = kValueTiles[k];
+  return (p.C >= kFlatC || k >= kTile32x32) &&
+         (int64_t)p.N * p.H * p.W * p.CG * nin < (int64_t)1 << 29 &&
+         taps * p.MT * nin < (int64_t)1 << 29 &&
+         ((int64_t)p.P + q.pos - 1) / q.pos * q.threads <= (int64_t)UINT32_MAX;
+}
+
 // AUTO's choice between the bitsliced kernel shape `algo` and the kernel on
 // float32 values: the tile of the latter, or -1. Both sides are estimated in
 // microseconds from the layer's sizes and the variant's operation counts; every
@@ -253,31 +273,21 @@ static int resolve_algo(const hobflops_conv_desc* d, const ConvVariant* v, int* 
 //    netlists' at 2.48 ns in the compact kernel, or two rounds of the split one;
 //    more: the chip's share of the fused netlist at 1.73 ns an instruction
 //    (4x224x224x3 -> 64: 73 us).
-// The 16x32 and 32x32 tiles alone handle fewer than kFlatC channels. Byte
-// offsets in that kernel are 32 bits wide, and a launch has fewer than 2^32
-// threads along x, of which that kernel takes 9 to 32 a position.
 static int value_plan(const ConvParams& p, const ConvVariant& v, int algo, int cus) {
-  const int64_t nin = 3 + v.wE + v.wF_in, taps = (int64_t)p.KH * p.KW * p.C;
-  if ((int64_t)p.N * p.H * p.W * p.CG * nin >= (int64_t)1 << 29 ||
-      taps * p.MT * nin >= (int64_t)1 << 29)
-    return -1;
-  const double t = (double)taps;
-  struct Tile {
-    int pos, mtiles, chains, threads;
+  const double t = (double)p.KH * p.KW * p.C;
+  struct Cost {
     double tap_ns, fixed_us;
   };
-  static const Tile kTiles[] = {
-      {112, 2, 28, 1024, 0.0, 11.0}, {56, 2, 14, 512, 10.0, 6.0}, {32, 2, 8, 512, 13.0, 4.0},
-      {32, 1, 4, 512, 18.0, 3.0},    {16, 1, 2, 512, 20.0, 2.5}};
+  static const Cost kCosts[] = {{0.0, 11.0}, {10.0, 6.0}, {13.0, 4.0}, {18.0, 3.0}, {20.0, 2.5}};
   int best = -1;
   double best_us = 0.0;
-  for (int k = p.C < kFlatC ? kTile32x32 : 0; k <= kTile16x32; ++k) {
-    const Tile& q = kTiles[k];
-    const int64_t nx = ((int64_t)p.P + q.pos - 1) / q.pos;
-    if (nx * q.threads > (int64_t)UINT32_MAX) continue;
-    const int64_t n = nx * ((p.MT + q.mtiles - 1) / q.mtiles);
+  for (int k = kTile112x64; k <= kTile16x32; ++k) {
+    if (!value_tile_ok(p, v, k)) continue;
+    const ValueTileShape& q = kValueTiles[k];
+    const Cost& c = kCosts[k];
+    const int64_t n = (((int64_t)p.P + q.pos - 1) / q.pos) * ((p.MT + q.mtiles - 1) / q.mtiles);
     const double rounds = (double)((n + cus - 1) / cus);
-    const double us = rounds * (t * (q.chains * 1.26 * v.value_ops + q.tap_ns) * 1e-3 + q.fixed_us);
+    const double us = rounds * (t * (q.chains * 1.26 * v.value_ops + c.tap_ns) * 1e-3 + c.fixed_us);
     if (best < 0 || us < best_us) {
       best = k;
       best_us = us;
@@ -318,16 +328,35 @@ static ConvParams conv_params(const hobflops_conv_desc* d) {
   return p;
 }
 
-int hobflops_conv2d_value_ops(const hobflops_conv_desc* d) {
+// The tile AUTO runs a descriptor in on values (>= 0), -1 if it runs bitsliced
+// or d->algo names a shape; or an error status.
+static int auto_tile(const hobflops_conv_desc* d, const ConvVariant** v, int* tile) {
   const int st = conv_check(d);
   if (st != HOBFLOPS_OK) return st;
-  const ConvVariant* v = find_conv(d);
-  if (!v) return HOBFLOPS_EUNSUPPORTED;
-  if (d->algo != HOBFLOPS_ALGO_AUTO) return 0;
+  *v = find_conv(d);
+  if (!*v) return HOBFLOPS_EUNSUPPORTED;
+  *tile = -1;
+  if (d->algo != HOBFLOPS_ALGO_AUTO) return HOBFLOPS_OK;
   int algo = 0, cus = 0;
-  const int st2 = resolve_algo(d, v, &algo, &cus);
-  if (st2 != HOBFLOPS_OK) return st2;
-  return value_plan(conv_params(d), *v, algo, cus) >= 0 ? v->value_ops : 0;
+  const int st2 = resolve_algo(d, *v, &algo, &cus);
+  if (st2 == HOBFLOPS_OK) *tile = value_plan(conv_params(d), **v, algo, cus);
+  return st2;
+}
+
+int hobflops_conv2d_value_ops(const hobflops_conv_desc* d) {
+  const ConvVariant* v = nullptr;
+  int tile = -1;
+  const int st = auto_tile(d, &v, &tile);
+  return st != HOBFLOPS_OK ? st : tile >= 0 ? v->value_ops : 0;
+}
+
+static_assert(HOBFLOPS_TILE_112X64 == kTile112x64 + 1 && HOBFLOPS_TILE_16X32 == kTile16x32 + 1);
+
+int hobflops_conv2d_value_tile(const hobflops_conv_desc* d) {
+  const ConvVariant* v = nullptr;
+  int tile = -1;
+  const int st = auto_tile(d, &v, &tile);
+  return st != HOBFLOPS_OK ? st : tile + 1;
 }
 
 int hobflops_conv2d_algo(const hobflops_conv_desc* d) {
@@ -379,6 +408,21 @@ int hobflops_conv2d(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
     if (tile >= 0) kalgo = kAlgoValue + tile;
   }
   return hip_status(v->launch(ifm, w, ofm, p, kalgo, (hipStream_t)stream));
+}
+
+int hobflops_conv2d_on_values(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm,
+                              const hobflops_conv_desc* d, int tile, void* stream) {
+  const int st = conv_check(d);
+  if (st != HOBFLOPS_OK) return st;
+  if (d->algo != HOBFLOPS_ALGO_AUTO || tile < HOBFLOPS_TILE_112X64 || tile > HOBFLOPS_TILE_16X32)
+    return HOBFLOPS_EINVAL;
+  if (!ifm || !w || !ofm) return HOBFLOPS_EINVAL;
+  if (!aligned(ifm) || !aligned(w) || !aligned(ofm)) return HOBFLOPS_EALIGN;
+  const ConvVariant* v = find_conv(d);
+  if (!v) return HOBFLOPS_EUNSUPPORTED;
+  const ConvParams p = conv_params(d);
+  if (!value_tile_ok(p, *v, tile - 1)) return HOBFLOPS_EUNSUPPORTED;
+  return hip_status(v->launch(ifm, w, ofm, p, kAlgoValue + tile - 1, (hipStream_t)stream));
 }
 
 int hobflops_muladd_supported(hobflops_fmt in_fmt, hobflops_fmt acc_fmt, int round) {

@@ -19,6 +19,7 @@ ACT_NONE, ACT_RELU = 0, 1
 ROUND_NEAREST_EVEN, ROUND_TOWARD_ZERO, ORDER_KY_KX_C = 0, 1, 0
 ALGO_AUTO, ALGO_FUSED, ALGO_SPLIT, ALGO_SPLIT_COMPACT = 0, 1, 2, 3
 OFM_PLANES, OFM_F32, OFM_CODE = 0, 1, 2
+TILE_112X64, TILE_56X64, TILE_32X64, TILE_32X32, TILE_16X32 = 1, 2, 3, 4, 5
 
 
 class HobflopsError(RuntimeError):
@@ -51,6 +52,7 @@ class PackJob(ctypes.Structure):
 EXPORTS = ("hobflops_plane_words", "hobflops_pack", "hobflops_pack_batch", "hobflops_unpack",
            "hobflops_conv2d",
            "hobflops_conv2d_supported", "hobflops_conv2d_algo", "hobflops_conv2d_value_ops",
+           "hobflops_conv2d_value_tile", "hobflops_conv2d_on_values",
            "hobflops_muladd", "hobflops_muladd_supported",
            "hobflops_netlist_ops", "hobflops_avgpool", "hobflops_avgpool_supported",
            "hobflops_avgpool_netlist_ops", "hobflops_wait_failures", "hobflops_set_wait_limit",
@@ -74,6 +76,8 @@ def lib():
         L.hobflops_conv2d_supported.argtypes = [ctypes.POINTER(ConvDesc)]
         L.hobflops_conv2d_algo.argtypes = [ctypes.POINTER(ConvDesc)]
         L.hobflops_conv2d_value_ops.argtypes = [ctypes.POINTER(ConvDesc)]
+        L.hobflops_conv2d_value_tile.argtypes = [ctypes.POINTER(ConvDesc)]
+        L.hobflops_conv2d_on_values.argtypes = [vp, vp, vp, ctypes.POINTER(ConvDesc), ci, vp]
         L.hobflops_muladd.argtypes = [vp, vp, vp, vp, i64, Fmt, Fmt, ci, vp]
         L.hobflops_muladd_supported.argtypes = [Fmt, Fmt, ci]
         L.hobflops_netlist_ops.argtypes = [Fmt, Fmt, ci] + [ctypes.POINTER(ci)] * 4
@@ -213,10 +217,8 @@ def conv_out_hw(d):
     return ((d.H + 2 * d.pad - d.KH) // d.stride + 1, (d.W + 2 * d.pad - d.KW) // d.stride + 1)
 
 
-def conv2d(ifm, w, d, out=None):
-    """ifm planes [N*H*W, ceil(C/32), NB_in], w planes [KH*KW*C, ceil(M/32), NB_in]
-    -> ofm planes [N*OH*OW, ceil(M/32), NB_out]; with d.ofm_kind OFM_F32 / OFM_CODE,
-    float32 values / int32 codes [N*OH*OW, M]."""
+def _conv_out(ifm, w, d, out):
+    """conv2d's output tensor (a new one for None), all three checked."""
     OH, OW = conv_out_hw(d)
     if out is None:
         if d.ofm_kind == OFM_PLANES:
@@ -230,6 +232,14 @@ def conv2d(ifm, w, d, out=None):
         _require(w, 4 * plane_words(d.KH * d.KW * d.C, d.M, d.in_fmt), "conv2d w")
         _require(out, 4 * (plane_words(d.N * OH * OW, d.M, d.out_fmt) if d.ofm_kind == OFM_PLANES
                            else d.N * OH * OW * d.M), "conv2d out")
+    return out
+
+
+def conv2d(ifm, w, d, out=None):
+    """ifm planes [N*H*W, ceil(C/32), NB_in], w planes [KH*KW*C, ceil(M/32), NB_in]
+    -> ofm planes [N*OH*OW, ceil(M/32), NB_out]; with d.ofm_kind OFM_F32 / OFM_CODE,
+    float32 values / int32 codes [N*OH*OW, M]."""
+    out = _conv_out(ifm, w, d, out)
     _check(lib().hobflops_conv2d(_ptr(ifm), _ptr(w), _ptr(out), ctypes.byref(d), _stream(ifm)))
     return out
 
@@ -255,6 +265,23 @@ def conv2d_value_ops(d):
     if rc < 0:
         _check(rc)
     return rc
+
+
+def conv2d_value_tile(d):
+    """The tile (TILE_*) ALGO_AUTO runs d in on float32 values; 0 if bitsliced."""
+    rc = lib().hobflops_conv2d_value_tile(ctypes.byref(d))
+    if rc < 0:
+        _check(rc)
+    return rc
+
+
+def conv2d_on_values(ifm, w, d, tile, out=None):
+    """conv2d on float32 values in the given tile (TILE_*), whichever kernel
+    ALGO_AUTO would pick: the same results."""
+    out = _conv_out(ifm, w, d, out)
+    _check(lib().hobflops_conv2d_on_values(_ptr(ifm), _ptr(w), _ptr(out), ctypes.byref(d), tile,
+                                           _stream(ifm)))
+    return out
 
 
 def muladd(a, b, c, n, in_fmt, acc_fmt, out=None, round=ROUND_NEAREST_EVEN):

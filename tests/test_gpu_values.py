@@ -1,10 +1,11 @@
 """The convolution on float32 values (AUTO's other kernel) against the oracle,
 bit for bit: every product of two finite (5,3) values and every sum of two
 finite (4,3) values, in both roundings; and every generated variant at the edges
-of the kernel's tiles, chunks and formats.
+of the kernel's tiles, chunks and formats, in every tile.
 
 conv2d_value_ops says whether AUTO takes that kernel; every case here is one
-where it does.
+where it does. AUTO takes the 16x32 tile for most small shapes; conv2d_on_values
+runs a given tile.
 """
 import numpy as np
 import pytest
@@ -19,19 +20,25 @@ pytestmark = pytest.mark.gpu
 ROUNDINGS = pytest.mark.parametrize("rnd", [0, 1], ids=["rne", "rtz"])
 
 
-def conv_on_values(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, rnd, kind=None):
-    """AUTO's convolution of code tensors (NHWC / HWIO), which must run on values
-    -> output codes [N, OH, OW, M] (kind OFM_F32: float32 bits)."""
+def tiles_of(hf, C):
+    """The tiles that take C channels, as the header says."""
+    return range(hf.TILE_32X32 if C < 16 else hf.TILE_112X64, hf.TILE_16X32 + 1)
+
+
+def conv_on_values(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, rnd, kind=None, tile=None):
+    """AUTO's convolution of code tensors (NHWC / HWIO), which must run on values,
+    or the given tile's -> output codes [N, OH, OW, M] (kind OFM_F32: float32
+    bits)."""
     N, H, W, C = qi.shape
     KH, KW, _, M = qw.shape
     kind = hf.OFM_PLANES if kind is None else kind
     d = hf.conv_desc(N, H, W, C, M, KH, KW, stride, pad, (wE, wi), (wE, wa), (wE, wo), act,
                      hf.ALGO_AUTO, round=rnd, ofm_kind=kind)
-    assert hf.conv2d_value_ops(d) > 0, "AUTO does not run this case on values"
+    assert tile or hf.conv2d_value_ops(d) > 0, "AUTO does not run this case on values"
     OH, OW = hf.conv_out_hw(d)
     pi = hf.pack(dev(qi.astype(np.uint32).view(np.int32).reshape(-1, C)), (wE, wi))
     pw = hf.pack(dev(qw.astype(np.uint32).view(np.int32).reshape(-1, M)), (wE, wi))
-    out = hf.conv2d(pi, pw, d)
+    out = hf.conv2d_on_values(pi, pw, d, tile) if tile else hf.conv2d(pi, pw, d)
     if kind == hf.OFM_PLANES:
         out = hf.unpack(out, N * OH * OW, M, (wE, wo), kind="code")
     return codes_of(out).reshape(N, OH, OW, M)
@@ -153,12 +160,13 @@ def test_sums_around_the_largest_number(v):
 
 
 # (N, H, W, C, M, K, stride, pad): one position and one kernel; 3 and 15 channels
-# (chunks across pixels); 16, 31, 33 channels; tiles of 16, 32, 56 and 112
-# positions with one position more or less; one, two and three words of kernels
-# with one kernel more or less; a stride, no padding, wide padding.
+# (chunks across pixels); 16, 31, 33 channels; 15, 16, 32, 33, 55 to 57, 111
+# and 113 positions (a tile more or less one); one, two and three words of
+# kernels with one kernel more or less; a stride, no padding, wide padding.
 EDGES = [(1, 1, 1, 200, 1, 1, 1, 0), (1, 5, 3, 3, 33, 3, 1, 1), (2, 4, 4, 15, 31, 3, 2, 1),
          (1, 4, 4, 16, 32, 3, 1, 1), (1, 3, 11, 31, 65, 3, 1, 1), (1, 7, 8, 33, 64, 3, 1, 1),
-         (2, 9, 9, 64, 40, 3, 2, 0), (1, 5, 7, 37, 96, 5, 1, 4)]
+         (2, 9, 9, 64, 40, 3, 2, 0), (1, 5, 7, 37, 96, 5, 1, 4), (1, 5, 11, 20, 63, 2, 1, 0),
+         (1, 3, 19, 16, 33, 3, 1, 1), (1, 3, 37, 33, 65, 1, 1, 0), (1, 1, 113, 17, 64, 3, 1, 1)]
 
 
 @pytest.mark.parametrize("v", variants.CONV_VARIANTS, ids=variants.conv_tag)
@@ -182,29 +190,54 @@ def test_every_variant_at_the_edges(v):
             qi, qw = orc.quantize_f32(ifm, wE, wi), orc.quantize_f32(w, wE, wi)
             kind = (hf.OFM_PLANES, hf.OFM_CODE, hf.OFM_F32)[n % 3]
             say(f"conv on values {variants.conv_tag(v)} {s} scale={scale} specials={specials}")
-            got = conv_on_values(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, rnd, kind)
             want = orc.conv2d(qi, qw, stride, pad, wE, wi, wa, wo, act, rnd=rnd)
             if kind == hf.OFM_F32:
                 want = orc.decode_f32(want, wE, wo).view(np.uint32).astype(np.uint64)
-            bad = np.argwhere(got != want)
-            assert bad.size == 0, f"{len(bad)} mismatches, first at {bad[0]}"
+            for tile in (None, *tiles_of(hf, C)):
+                got = conv_on_values(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, rnd, kind, tile)
+                bad = np.argwhere(got != want)
+                assert bad.size == 0, f"tile {tile}: {len(bad)} mismatches, first at {bad[0]}"
 
 
-def test_large_tiles():
-    """The 112x64 and 56x64 tiles (wide layers), ragged at both ends."""
+@pytest.mark.parametrize("v", [(5, 10, 11, 11, 0, 0), (5, 3, 4, 4, 0, 0), (5, 5, 6, 6, 0, 1),
+                               (5, 10, 21, 21, 0, 0), (4, 3, 7, 7, 0, 0)], ids=variants.conv_tag)
+def test_large_tiles(v):
+    """Layers of many workgroups, ragged at both ends, in the 112x64, 56x64 and 32x64
+    tiles: sums in float64 and in float32, products rounded and exact, toward zero,
+    sums tracked."""
     hf = need_gpu()
+    wE, wi, wa, wo, act, rnd = v
     for N, H, W, C, M in ((3, 47, 50, 64, 192), (2, 29, 31, 96, 250)):
         g = np.random.default_rng([18, C])
         ifm = np.maximum(g.standard_normal((N, H, W, C)), 0).astype(np.float32)
         w = (g.standard_normal((3, 3, C, M)) * 0.05).astype(np.float32)
-        qi, qw = orc.quantize_f32(ifm, 5, 10), orc.quantize_f32(w, 5, 10)
-        say(f"conv on values, large tiles {N}x{H}x{W}x{C} -> {M}")
-        got = conv_on_values(hf, qi, qw, 1, 1, 5, 10, 11, 11, 0, 0)
-        pts = np.stack([g.integers(0, q, 8192) for q in got.shape], 1).astype(np.int64)
+        qi, qw = orc.quantize_f32(ifm, wE, wi), orc.quantize_f32(w, wE, wi)
+        pts = np.stack([g.integers(0, q, 8192) for q in (N, H, W, M)], 1).astype(np.int64)
         pts[:64, 2], pts[64:128, 1], pts[128:192, 3] = W - 1, H - 1, M - 1
-        want = orc.conv2d_points(qi, qw, pts, 1, 1, 5, 10, 11, 11)
-        bad = np.flatnonzero(got[pts[:, 0], pts[:, 1], pts[:, 2], pts[:, 3]] != want)
-        assert bad.size == 0, f"{bad.size} mismatches; first at {pts[bad[0]]}"
+        pts[192:256] = [(N - 1, H - 1, W - 1 - i % 16, M - 1 - i // 16) for i in range(64)]
+        want = orc.conv2d_points(qi, qw, pts, 1, 1, wE, wi, wa, wo, act, rnd=rnd)
+        for tile in (hf.TILE_112X64, hf.TILE_56X64, hf.TILE_32X64):
+            say(f"conv on values, large tiles {N}x{H}x{W}x{C} -> {M} tile {tile}")
+            got = conv_on_values(hf, qi, qw, 1, 1, wE, wi, wa, wo, act, rnd, tile=tile)
+            bad = np.flatnonzero(got[pts[:, 0], pts[:, 1], pts[:, 2], pts[:, 3]] != want)
+            assert bad.size == 0, f"{bad.size} mismatches; first at {pts[bad[0]]}"
+
+
+def test_tile_queries():
+    """The tile AUTO takes, and what a tile refuses; nothing is launched."""
+    hf = need_gpu()
+
+    def d(C, algo=hf.ALGO_AUTO, **kw):
+        return hf.conv_desc(8, 56, 56, C, 64, 3, 3, 1, 1, (5, 3), (5, 4), (5, 4), 0, algo, **kw)
+    assert hf.conv2d_value_tile(d(64)) == hf.TILE_112X64  # 224 tiles, one round of 256 CUs
+    assert hf.conv2d_value_tile(d(64, hf.ALGO_FUSED)) == 0
+    x = dev(np.zeros(8 * 56 * 56 * 2 * 11, np.int32))
+    w = dev(np.zeros(9 * 64 * 2 * 11, np.int32))
+    for desc, tile, status in ((d(64), 0, -1), (d(64), 6, -1), (d(64, hf.ALGO_FUSED), 1, -1),
+                               (d(15), hf.TILE_112X64, -2), (d(15), hf.TILE_32X64, -2)):
+        with pytest.raises(hf.HobflopsError) as e:
+            hf.conv2d_on_values(x, w, desc, tile)
+        assert e.value.status == status
 
 
 def test_launch_limit():
@@ -215,3 +248,4 @@ def test_launch_limit():
         d = hf.conv_desc(1, 1, 1, 64, 64, 1, 1, 1, pad, (5, 10), (5, 21), (5, 21), 0,
                          hf.ALGO_AUTO, round=0)
         assert (hf.conv2d_value_ops(d) > 0) == on_values, pad
+        assert (hf.conv2d_value_tile(d) > 0) == on_values, pad

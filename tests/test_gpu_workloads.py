@@ -5,8 +5,9 @@ Each workload runs whole on the GPU through the C ABI, at its real shape:
     (5,3), as well as in (5,4): every output;
   * the element-wise a*b+c sweep: 2^24 triples per format, six formats: every
     triple;
-  * the ResNet layer 8x56x56x64 -> 64 in the benchmark's launch (split kernel,
-    float32 OFM written by the epilogue): every output;
+  * the ResNet layer 8x56x56x64 -> 64 in the benchmark's launch (AUTO's kernel on
+    float32 values, float32 OFM written by the epilogue) and in the split
+    kernel: every output;
   * the paper's MobileNets-shaped layer 14x14x512 -> 512, 3x3, stride 2, for
     every generated MAC type of the type sweep: every output;
   * the mantissa sweep: 4x224x224x3 -> 64 and 4x28x28x256 -> 512, 3x3, for
@@ -104,28 +105,33 @@ def conv_codes_of(hf, qi, qw, stride, pad, wE, wi, wa, wo, act, algo, rnd):
 
 def test_resnet_layer_every_output():
     """8x56x56x64 -> 64, 3x3, (5,3) -> (5,4), in the benchmark's launch: one
-    pack launch for the IFM and the weights, the split kernel, float32 OFM
-    from the epilogue. Every output's float32 bits and code against the
-    oracle's full convolution (all host threads)."""
+    pack launch for the IFM and the weights, AUTO's kernel (on float32 values,
+    112x64 tiles), float32 OFM from the epilogue; and in the split kernel. Every
+    output's float32 bits and code against the oracle's full convolution (all
+    host threads)."""
     hf = need_gpu()
     s = I.RESNET_CONV_SHAPE
     ifm, w = I.resnet_conv_inputs()
     P = s.N * s.OH * s.OW
-    say("resnet layer 8x56x56x64->64 every output (split kernel, float32 OFM)")
+    say("resnet layer 8x56x56x64->64 every output (AUTO and split kernel, float32 OFM)")
     x_ifm, x_w = dev(ifm.reshape(-1, s.C)), dev(w.reshape(-1, s.M))
     pi, pw = hf.pack_batch([x_ifm, x_w], (5, 3))
     vals = {}
-    for kind in (hf.OFM_F32, hf.OFM_CODE):
-        d = hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad, (5, 3), (5, 4),
-                         (5, 4), hf.ACT_NONE, hf.ALGO_SPLIT, ofm_kind=kind)
-        vals[kind] = hf.conv2d(pi, pw, d).cpu().numpy().view(np.uint32)
+    for algo in (hf.ALGO_AUTO, hf.ALGO_SPLIT):
+        for kind in (hf.OFM_F32, hf.OFM_CODE):
+            d = hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad, (5, 3),
+                             (5, 4), (5, 4), hf.ACT_NONE, algo, ofm_kind=kind)
+            if algo == hf.ALGO_AUTO:
+                assert hf.conv2d_value_tile(d) == hf.TILE_112X64
+            vals[algo, kind] = hf.conv2d(pi, pw, d).cpu().numpy().view(np.uint32)
     qi = threaded(orc.quantize_f32, ifm, fixed=(5, 3))
     qw = orc.quantize_f32(w, 5, 3)
     want = orc.conv2d(qi, qw, s.stride, s.pad, 5, 3, 4, 4).reshape(P, s.M)
-    bad = np.argwhere(vals[hf.OFM_CODE].astype(np.uint64) != want)
-    assert bad.size == 0, f"{len(bad)} mismatching codes of {want.size}; first at {bad[0]}"
     want_f = threaded(orc.decode_f32, want, fixed=(5, 4)).view(np.uint32)
-    assert np.array_equal(vals[hf.OFM_F32], want_f)
+    for algo in (hf.ALGO_AUTO, hf.ALGO_SPLIT):
+        bad = np.argwhere(vals[algo, hf.OFM_CODE].astype(np.uint64) != want)
+        assert bad.size == 0, f"{len(bad)} mismatching codes of {want.size}; first at {bad[0]}"
+        assert np.array_equal(vals[algo, hf.OFM_F32], want_f)
 
 
 def test_stack_layer_one_every_kernel_shape():
@@ -140,7 +146,7 @@ def test_stack_layer_one_every_kernel_shape():
     qi, qw = orc.quantize_f32(ifm, 5, 3), orc.quantize_f32(w, 5, 3)
     d = hf.conv_desc(s.N, s.H, s.W, s.C, s.M, s.KH, s.KW, s.stride, s.pad, (5, 3), (5, 4), (5, 5),
                      1, hf.ALGO_AUTO)
-    assert hf.conv2d_algo(d) == hf.ALGO_SPLIT_COMPACT
+    assert hf.conv2d_algo(d) == hf.ALGO_SPLIT_COMPACT and hf.conv2d_value_tile(d) == 0
     outs = {}
     for algo in (hf.ALGO_AUTO, hf.ALGO_FUSED, hf.ALGO_SPLIT, hf.ALGO_SPLIT_COMPACT):
         say(f"stack layer 1 16x56x56x64->64 algo={algo}")
