@@ -89,16 +89,37 @@ def test_avgpool_edge_shapes(shape):
     assert np.array_equal(got, orc.avgpool(x, 5, 4, 5, 4))
 
 
-@pytest.mark.parametrize("rnd", [variants.RNE, variants.RTZ], ids=["rne", "rtz"])
+@pytest.mark.parametrize("v", variants.POOL_VARIANTS, ids=variants.pool_tag)
 @pytest.mark.parametrize("groups", [6144, 6145])
-def test_avgpool_both_kernels(groups, rnd):
+def test_avgpool_both_kernels(groups, v):
     """The last group count of the kernel on values and the first of the
     bitsliced one, an odd map."""
     hf = need_gpu()
-    x = pool_inputs(groups, groups, 1, 3, 20, 5, 4, specials=0.01)
-    say(f"avgpool {groups} groups rnd={rnd}")
-    got = run_pool(hf, x, 5, 4, 4, 4, rnd)
-    assert np.array_equal(got, orc.avgpool(x, 5, 4, 4, 4, rnd=rnd))
+    wE, wi, wa, wo, rnd = v
+    x = pool_inputs(groups, groups, 1, 3, 20, wE, wi, specials=0.01)
+    say(f"avgpool {groups} groups {variants.pool_tag(v)}")
+    got = run_pool(hf, x, wE, wi, wa, wo, rnd)
+    assert np.array_equal(got, orc.avgpool(x, wE, wi, wa, wo, rnd=rnd))
+
+
+@pytest.mark.parametrize("rnd", [variants.RNE, variants.RTZ], ids=["rne", "rtz"])
+def test_avgpool_every_pair_of_codes_on_values(rnd):
+    """Every pair of (4,4) codes, 6144 groups a call, so that the kernel on values
+    takes them; then the pairs of canonical finite codes alone, whose waves hold no
+    infinity or NaN."""
+    hf = need_gpu()
+    codes = np.arange(1 << 11, dtype=np.uint64)
+    finite = codes[(codes >> np.uint64(9) == 1) | (codes & np.uint64(0x6FF) == 0)]
+    n = 6144 * 32
+    for c in (codes, finite):
+        a, b = (v.reshape(-1) for v in np.meshgrid(c, c, indexing="ij"))
+        say(f"avgpool every pair of (4,4) codes on values, {c.size} codes rnd={rnd}")
+        for lo in range(0, a.size, n):
+            x = np.stack([a[lo:lo + n], b[lo:lo + n]]).reshape(1, 1, 2, -1)
+            got = run_pool(hf, x, 4, 4, 4, 4, rnd)
+            want = orc.avgpool(x, 4, 4, 4, 4, rnd=rnd)
+            bad = np.flatnonzero(got != want)
+            assert bad.size == 0, f"{bad.size} mismatches; first at {lo + bad[0]}"
 
 
 @pytest.mark.parametrize("v", variants.POOL_VARIANTS, ids=variants.pool_tag)
