@@ -589,7 +589,7 @@ hipError_t launch_pool_{tag}(const uint32_t* in, uint32_t* out, const PoolParams
   const int64_t lanes = (int64_t)p.N * p.CG;
   if (lanes <= kPoolValueGroups) {{
     hipLaunchKernelGGL(avgpool_value_kernel<pool_{tag}::V>, dim3((unsigned)((lanes + 7) / 8)), dim3(256),
-                       0, stream, in, out, p, ValueMath<pool_{tag}::V>::bound((double)p.HW));
+                       0, stream, in, out, p);
     return hipGetLastError();
   }}
   hipLaunchKernelGGL(avgpool_kernel<pool_{tag}::V>, dim3((unsigned)((lanes + 255) / 256)), dim3(256),

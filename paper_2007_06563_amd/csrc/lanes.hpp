@@ -58,6 +58,17 @@ __device__ __forceinline__ uint32_t row_xor(uint32_t x) {
   }
 }
 
+// The largest x of the wave, the same in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  x = max(x, row_xor<0>(x));
+  x = max(x, row_xor<1>(x));
+  x = max(x, row_xor<2>(x));
+  x = max(x, row_xor<3>(x));
+  auto row = [&](int lane) { return (uint32_t)__builtin_amdgcn_readlane(x, lane); };
+  const uint32_t a = max(row(0), row(16)), b = max(row(32), row(48));
+  return max(a, b);
+}
+
 // The stages d = 8, 4, 2, 1 on N words.
 template <int N>
 __device__ __forceinline__ void row_transpose(uint32_t (&x)[N], const RowT& t) {

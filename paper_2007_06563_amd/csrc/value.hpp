@@ -34,10 +34,15 @@
 //    flushing it before rounding is the same. Of float64's operations only
 //    products are flushed, so there the sum passes through one.
 //  - Zero signs are IEEE's in every step.
-//  - Overflow and inputs that are infinite or NaN do not fit this: a workgroup
-//    that meets such an input, or whose inputs are so large that a sum could
-//    leave the format's range, computes its tile again step by step with the
-//    range checks written out (mac_checked).
+//  - Overflow and inputs that are infinite or NaN do not fit this. The workgroup
+//    knows the largest operands staged so far and the chunks of taps that hold an
+//    infinity or NaN; such a chunk, and one whose sums could leave the format's range
+//    by those operands and the sums before it, takes a slower route (careful_chunk),
+//    wave by wave. The bitsliced kernels take one time for all inputs; this one:
+//    8x56x56x64 -> 64, 576 taps, (5,3) -> (5,4): ordinary inputs 147 us, an infinity
+//    in each image 151, 1 % infinities or nothing but NaN 186, the largest finite
+//    number in each image 204, bitsliced 157; (4,3) -> (4,4) with sums that overflow
+//    everywhere 216, bitsliced 151.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <math.h>
@@ -79,16 +84,24 @@ struct ValueMath {
   static constexpr int kScaleW = kScale - kScaleX + kLift;
   // exponent of the first power of two out of range
   static constexpr int kTop = (1 << wE) - kBias;
-  // A narrow exponent range under a long fraction (2^(wF+2) times a product of
-  // up to 2^3 leaves the range): no useful bound of the sums follows from the
-  // largest operands, so the largest sum is tracked (half an instruction a MAC).
-  static constexpr bool kTrack = wE < 5 && wA + 5 > kTop;
-  static_assert(!(kTrack && kWide), "float64 sums are not tracked");
-  // The bits of the smallest sum out of range before its rounding, scaled: to
-  // nearest, half a unit in the last place below 2^kTop rounds up to it (a tie goes
-  // to 2^kTop, whose last place is even).
+  // The smallest sum out of range before its rounding, scaled: to nearest, half a
+  // unit in the last place below 2^kTop rounds up to it (a tie goes to 2^kTop, whose
+  // last place is even).
   static constexpr uint32_t kOverflow =
       ((uint32_t)(127 + kTop + kScale) << 23) - (kRtz ? 0u : 1u << (k - 1));
+  // Sums that start at |acc| <= A and take up to 32 terms of at most P (before
+  // their rounding) stay in range if A + 32 P < kRoom 2^kTop. With u half a unit in
+  // the last place of 1, a term grows by 1 + u when rounded, and a rounding adds at
+  // most 2^kTop u / 2 while the sums are in range, or a factor of 1 + u.
+  static constexpr double room() {
+    if (kRtz) return 1.0 - 0x1p-20;  // the estimate's own rounding
+    const double u = 1.0 / (double)(2LL << wA);
+    double f = 1.0;
+    for (int i = 0; i < 33; ++i) f /= 1.0 + u;
+    const double a = 1.0 - 16.0 * u;
+    return (1.0 - 0x1p-20) / (1.0 + u) * (a > f ? a : f);
+  }
+  static constexpr float kRoom = (float)room();
 
   // MODE: float32 rounding nearest or toward zero; float32 results and float64
   // products below the smallest normal number flushed, such operands read as
@@ -112,28 +125,45 @@ struct ValueMath {
     return kLift ? r * pow2f(-kLift) : r;
   }
   // acc + r in the format; a float64 accumulator is scaled by 2^-896 more, so
-  // that 2^-1022 is the format's smallest normal number
+  // that 2^-1022 is the format's smallest normal number. With kTrack, track takes the
+  // largest magnitude of the term and of the sum before its rounding, NaN apart.
+  template <bool kTrack>
   static __device__ __forceinline__ Acc add(Acc acc, float r, float& track) {
     if constexpr (kWide) {
       // float64 additions keep numbers below 2^-1022, the multiplication does not
-      const double s = __builtin_fma(acc, 0x1p896, (double)r) * 0x1p-896;
+      const double t = __builtin_fma(acc, 0x1p896, (double)r);
+      if constexpr (kTrack) track_max(track, (float)t, r);
+      const double s = t * 0x1p-896;
       const double u = s * (double)((1LL << (52 - wA)) + 1);
       const double v = u - s;
       return u - v;
     } else {
       const float s = acc + r;
-      if constexpr (kTrack) asm("v_max_f32 %0, %1, |%2|" : "=v"(track) : "v"(track), "v"(s));
+      if constexpr (kTrack) track_max(track, s, r);
       if constexpr (kRtz) return trunc(s);
       const float u = s * (float)((1 << k) + 1);
       const float v = u - s;
       return u - v;
     }
   }
-  // the accumulator's value, unscaled (exact)
+  static __device__ __forceinline__ void track_max(float& track, float a, float b) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(track) : "v"(a), "v"(b));
+  }
+  // the accumulator's value, unscaled (exact), and back
   static __device__ __forceinline__ float value(Acc acc) {
     if constexpr (kWide) return (float)(acc * __builtin_ldexp(1.0, 896 - kScale));
     return acc * pow2f(-kScale);
   }
+  static __device__ __forceinline__ Acc scaled(float v) {
+    if constexpr (kWide) return (double)v * __builtin_ldexp(1.0, kScale - 896);
+    return v * pow2f(kScale);
+  }
+  // the accumulator's magnitude, scaled like a float32 one; NaN as it is
+  static __device__ __forceinline__ float magnitude(Acc acc) {
+    if constexpr (kWide) return __builtin_fabsf((float)(acc * 0x1p896));
+    return __builtin_fabsf(acc);
+  }
+  static __device__ __forceinline__ bool finite(float v) { return v - v == 0.0f; }
   // The same step on unscaled values with every check written out: infinities
   // and NaN follow IEEE-754, overflow gives a signed infinity.
   static __device__ __forceinline__ float range(float v) {
@@ -165,17 +195,11 @@ struct ValueMath {
   // sum of `taps` of them can reach 2^kTop: rounding is monotone, so the sums
   // stay below those of `taps` equal terms P rounded up, which grow by P (1 + u)
   // a tap, u half a unit in the last place, and stop growing at 2^(wF + 2) P,
-  // where P is less than half a unit of the sum. With kTrack the sums are
-  // looked at themselves.
-  static float bound(double taps) {
+  // where P is less than half a unit of the sum.
+  static double bound(double taps) {
     const double u = ldexp(1.0, -(wA + 1));
-    double grow = 1.0;
-    if (!kTrack) {
-      grow = taps * (kRtz ? 1.0 : exp(2.0 * taps * u));
-      const double stop = ldexp(1.0, wA + 2);
-      grow = grow < stop ? grow : stop;
-    }
-    return (float)(ldexp(1.0, kTop) * (1.0 - 4.0 * u) / grow);
+    const double grow = taps * (kRtz ? 1.0 : exp(2.0 * taps * u)), stop = ldexp(1.0, wA + 2);
+    return ldexp(1.0, kTop) * (1.0 - 4.0 * u) / (grow < stop ? grow : stop);
   }
 };
 
@@ -233,7 +257,12 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
   constexpr bool kHigh = NIN > 16;  // a second plane word a lane
   __shared__ float xs[2][T::kXSets * 4][kRow];
   __shared__ float ws[2][T::kKern][kRow];
-  __shared__ uint32_t largest[4];  // magnitudes of x and w, largest sum, any infinity or NaN
+  __shared__ float nonfinite[RM * RP][T::kThreads];  // see the careful step
+  // What the staging waves found (see `found`): the largest finite codes of x and of
+  // w so far, their signs apart; the number of chunks from which on sums have to be
+  // looked at or, while that is not so, of chunks up to the last one with an infinity
+  // or NaN; and the latter number.
+  __shared__ alignas(16) uint32_t seen[4];
 
   const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -241,7 +270,7 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
   const int p0 = blockIdx.x * T::kPos, mt0 = blockIdx.y * (RM * WM);
   const int taps = p.KH * p.KW * p.C;
   const int nch = kFlat ? (taps + 31) / 32 : p.KH * p.KW * p.CG;
-  if (tid < 4) largest[tid] = 0u;
+  if (tid < 4) seen[tid] = 0u;
 
   // staging: this lane's group of a set, and its plane
   const int row = lane >> 4, l = lane & 15;
@@ -268,8 +297,6 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
     const uint32_t at = (uint32_t)(n * p.H + e.x) * (uint32_t)p.W + (uint32_t)e.y;
     xoff[i] = (at * (uint32_t)(p.CG * NIN) + min(l, NIN - 1)) * 4u;
   }
-  uint32_t mx = 0u, mw = 0u;         // largest magnitudes staged by this lane
-  uint32_t any = 0u, special = 0u;  // all its plane words; infinities and NaN among gathered codes
 
   struct Chunk {
     int ky, kx, cg, tap0, nc;
@@ -334,20 +361,42 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
     __builtin_memcpy(q, src, 4 * NIN);
 #pragma unroll
     for (int b = 0; b < NIN; ++b) code |= __builtin_amdgcn_ubfe(q[b], ch, 1) << b;
-    special |= ok ? code >> (NIN - 1) : 0u;
     return ok ? code : 0u;
   };
-  auto stage = [&](const Chunk& c, Raw& raw, int buf, auto checked) {
-    constexpr bool kChecked = decltype(checked)::value;
-    auto put_x = [&](int i, uint32_t code) {
-      const uint32_t v = decode_scaled<A::wE, A::wI, A::kScaleX, kChecked>(code);
-      mx = max(mx, v & 0x7FFFFFFFu);
-      xs[buf][i][j] = __uint_as_float(v);
+  // Reports the largest codes of x and of w that a lane staged for chunk ch, special if
+  // one of the wave's is an infinity or NaN (cx, cw are then the largest finite ones).
+  constexpr uint32_t kSignBit = 1u << (A::wE + A::wI), kSpecial = 4u * kSignBit;
+  auto found = [&](uint32_t cx, uint32_t cw, bool special, int ch) {
+    volatile uint32_t* const s = &seen[0];
+    const uint32_t ux = wave_max(cx), uw = wave_max(cw);
+    if (lane != 0) return;
+    if (special) s[3] = (uint32_t)(ch + 1);
+    atomicMax(&seen[0], ux);
+    atomicMax(&seen[1], uw);
+    __threadfence_block();
+    // read after both: of two waves that each raise one, the later finds both
+    const float big = __uint_as_float(decode_scaled<A::wE, A::wI, A::kScaleX, false>(s[0])) *
+                      __uint_as_float(decode_scaled<A::wE, A::wI, A::kScaleW, false>(s[1]));
+    if (special || !(big < bound)) atomicMax(&seen[2], big < bound ? (uint32_t)(ch + 1) : ~0u);
+  };
+  // The same number, computed where it is used: the addresses of rarely taken
+  // branches then do not hold registers throughout the loop.
+  auto here = [](int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  // Raw words of chunk ch -> float32 values of buffer ch & 1. Infinities and NaN are
+  // noticed by their codes, which are larger than the finite ones': sx and sw are the
+  // largest ones that earlier chunks are known to hold.
+  auto stage = [&](const Chunk& c, Raw& raw, int ch, uint32_t sx, uint32_t sw) {
+    const int buf = ch & 1;
+    auto put_x = [&](int i, int j, uint32_t code, auto checked) {
+      xs[buf][i][j] = __uint_as_float(
+          decode_scaled<A::wE, A::wI, A::kScaleX, decltype(checked)::value>(code));
     };
-    auto put_w = [&](int kern, int t, uint32_t code) {
-      const uint32_t v = decode_scaled<A::wE, A::wI, A::kScaleW, kChecked>(code);
-      mw = max(mw, v & 0x7FFFFFFFu);
-      ws[buf][kern][t ^ 2] = __uint_as_float(v);  // see the MAC
+    auto put_w = [&](int kern, int t, uint32_t code, auto checked) {
+      ws[buf][kern][t ^ 2] = __uint_as_float(  // see the MAC
+          decode_scaled<A::wE, A::wI, A::kScaleW, decltype(checked)::value>(code));
     };
     const uint32_t keep = c.nc < 32 ? (1u << c.nc) - 1u : ~0u;
     // all of this wave's sets through the transpose together: its steps depend
@@ -370,8 +419,6 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
       Q[X + i] = 0u;
       if constexpr (kHigh) Q[X + i] = t < c.nc && l + 16 < NIN ? raw.w[i][1] : 0u;
     }
-#pragma unroll
-    for (int i = 0; i < X + WS; ++i) any |= kHigh ? Q[i] : P[i];
     row_transpose(P, rt);
     if constexpr (kHigh) row_transpose(Q, rt);
 #pragma unroll
@@ -381,132 +428,268 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
       P[i] = a;
       Q[i] = b;
     }
+    uint32_t a[XS], b[XS];  // the codes of groups h and 2 + h of the sets of x
 #pragma unroll
     for (int i = 0; i < XS; ++i) {
       const int s = wave + i * NW;
       if (T::kXSets % NW != 0 && s >= T::kXSets) break;  // uniform
       if constexpr (kFlat) {
-        put_x(4 * s + h, gather(c, 4 * s + h));
-        put_x(4 * s + 2 + h, gather(c, 4 * s + 2 + h));
+        a[i] = gather(c, 4 * s + h);
+        b[i] = gather(c, 4 * s + 2 + h);
       } else {
-        put_x(4 * s + h, P[i]);
-        put_x(4 * s + 2 + h, Q[i]);
+        a[i] = P[i];
+        b[i] = Q[i];
       }
     }
+    // the largest codes, their signs apart: of all, or of the finite ones
+    auto put_all = [&](uint32_t& cx, uint32_t& cw, int lane, auto checked) {
+      const int j = lane & 31, h = lane >> 5;
+      auto key = [&](uint32_t code) {
+        code &= ~kSignBit;
+        return decltype(checked)::value && code >= kSpecial ? 0u : code;
+      };
+      cx = cw = 0u;
 #pragma unroll
-    for (int i = 0; i < WS; ++i) {
-      const int s = wave + i * NW;
-      if (T::kWSets % NW != 0 && s >= T::kWSets) break;  // uniform
-      const int kern = (s >> 3) * 32 + j, t0 = 4 * (s & 7) + h;
-      put_w(kern, t0, P[X + i]);
-      put_w(kern, t0 + 2, Q[X + i]);
+      for (int i = 0; i < XS; ++i) {
+        const int s = wave + i * NW;
+        if (T::kXSets % NW != 0 && s >= T::kXSets) break;  // uniform
+        put_x(4 * s + h, j, a[i], checked);
+        put_x(4 * s + 2 + h, j, b[i], checked);
+        cx = max(cx, max(key(a[i]), key(b[i])));
+      }
+#pragma unroll
+      for (int i = 0; i < WS; ++i) {
+        const int s = wave + i * NW;
+        if (T::kWSets % NW != 0 && s >= T::kWSets) break;  // uniform
+        const int kern = (s >> 3) * 32 + j, t0 = 4 * (s & 7) + h;
+        put_w(kern, t0, P[X + i], checked);
+        put_w(kern, t0 + 2, Q[X + i], checked);
+        cw = max(cw, max(key(P[X + i]), key(Q[X + i])));
+      }
+    };
+    uint32_t cx, cw;
+    put_all(cx, cw, lane, std::false_type{});
+    if (__builtin_expect(__any(cx > sx || cw > sw), 0)) {
+      const bool special = __any(max(cx, cw) >= kSpecial);
+      if (special) put_all(cx, cw, here(lane), std::true_type{});
+      found(cx, cw, special, ch);
     }
   };
 
-  // All chunks in order; `four` takes the operands of four taps at a time, or
-  // with kChecked `one` those of a single tap (small code: it runs rarely).
-  auto run = [&](auto checked, auto&& four, auto&& one) {
-    constexpr bool kChecked = decltype(checked)::value;
-    // step ch computes chunk ch and stages chunk ch + 1; the first only stages
-    Chunk nx{0, 0, 0, 0, kFlat ? min(32, taps) : min(32, p.C)};
-    int nq = 0;  // groups of four taps of the chunk to compute
-    Raw raw;
-    for (int ch = -1; ch < nch; ++ch) {
-      const bool more = ch + 1 < nch;
-      if (more) fetch(nx, raw);
-      const lds_f32* xb = (const lds_f32*)&xs[ch & 1][(wp * 2 + h) * RP][0];
-      const lds_f32* wb = (const lds_f32*)&ws[ch & 1][wm * RM * 32 + j][0];
-      if constexpr (kChecked) {
-#pragma unroll 1
-        for (int t = 0; t < 4 * nq; ++t) {
-          float xv[RP], wv[RM];
-#pragma unroll
-          for (int r = 0; r < RP; ++r) xv[r] = xb[r * kRow + t];
-#pragma unroll
-          for (int m = 0; m < RM; ++m) wv[m] = wb[m * 32 * kRow + (t ^ 2)];
-          one(xv, wv);
-        }
-      } else if (nq > 0) {
-        auto load = [&](int q, f32x4(&xv)[RP], f32x4(&wv)[RM]) {
-#pragma unroll
-          for (int r = 0; r < RP; ++r) xv[r] = *(const lds_f32x4*)(xb + r * kRow + 4 * q);
-#pragma unroll
-          for (int m = 0; m < RM; ++m) wv[m] = *(const lds_f32x4*)(wb + m * 32 * kRow + 4 * q);
-        };
-        // operands of the next four taps are requested before this four's MACs
-        f32x4 xa[RP], wa[RM], xc[RP], wc[RM];
-        load(0, xa, wa);
-        int q = 0;
-        for (; q + 2 <= nq; q += 2) {
-          load(q + 1, xc, wc);
-          four(xa, wa);
-          load(q + 2 < nq ? q + 2 : q, xa, wa);
-          four(xc, wc);
-        }
-        if (q < nq) four(xa, wa);
-      }
-      if (more) stage(nx, raw, (ch + 1) & 1, checked);
-      nq = (nx.nc + 3) >> 2;
-      advance(nx);
-      __syncthreads();
-    }
-  };
-  auto nothing = [](const auto&, const auto&) {};
-
-  float out[RM][RP];
   A::set_mode();
-  bool fits;
-  {
-    typename A::Acc acc[RM][RP];
-    float track = 0.0f;  // largest sum (kTrack)
+  typename A::Acc acc[RM][RP];
 #pragma unroll
-    for (int m = 0; m < RM; ++m)
+  for (int m = 0; m < RM; ++m)
 #pragma unroll
-      for (int r = 0; r < RP; ++r) acc[m][r] = 0;
-    run(std::false_type{}, [&](const f32x4(&xv)[RP], const f32x4(&wv)[RM]) {
+    for (int r = 0; r < RP; ++r) acc[m][r] = 0;
+
+  // The MACs of four taps.
+  auto four = [&](const f32x4(&xv)[RP], const f32x4(&wv)[RM]) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < 4; ++t) {
 #pragma unroll
-        for (int m = 0; m < RM; ++m) {
-          // weights lie two taps apart from the IFM values in their group of
-          // four, so that the two operands of a tap, each loaded four to an
-          // aligned register quad, come from different VGPR banks
-          const float wt = wv[m][t ^ 2], wk = A::prescale(wt);
+      for (int m = 0; m < RM; ++m) {
+        // weights lie two taps apart from the IFM values in their group of
+        // four, so that the two operands of a tap, each loaded four to an
+        // aligned register quad, come from different VGPR banks
+        const float wt = wv[m][t ^ 2], wk = A::prescale(wt);
+        float none = 0.0f;
 #pragma unroll
-          for (int r = 0; r < RP; ++r)
-            acc[m][r] = A::add(acc[m][r], A::product(wt, wk, xv[r][t]), track);
-        }
+        for (int r = 0; r < RP; ++r)
+          acc[m][r] = A::template add<false>(acc[m][r], A::product(wt, wk, xv[r][t]), none);
       }
-    }, nothing);
-    // the largest operands of the workgroup's tile decide whether any product
-    // or sum can have left the format's range
-    atomicMax(&largest[0], mx);
-    atomicMax(&largest[1], mw);
-    if constexpr (A::kTrack) atomicMax(&largest[2], __float_as_uint(track));
-    if ((l == ((NIN - 1) & 15) && any != 0u) || special != 0u) largest[3] = 1u;
-    __syncthreads();
-    const float big = __uint_as_float(largest[0]) * pow2f(-A::kScaleX) *
-                      (__uint_as_float(largest[1]) * pow2f(-A::kScaleW));
-    fits = big < bound && largest[3] == 0u;
-    if constexpr (A::kTrack)
-      fits = fits && largest[2] < A::kOverflow;
+    }
+  };
+
+  // A chunk with an infinity or NaN among the workgroup's operands, or (kTrack) in
+  // which a sum may leave the range. The steps of `four` make NaN of a special
+  // operand and of the chain that meets it, for good; what IEEE-754 makes of that
+  // chain (an infinity of either sign, or NaN) comes from the plain sum of its
+  // products, whose finite part is not used, kept beside the accumulator: in LDS
+  // between such chunks. Sums out of range are looked for after each few taps, which
+  // are then taken again one by one with the range checks written out.
+  bool kept = false;  // nonfinite is set (uniform over the wave)
+  auto careful_chunk = [&](int buf, int nt, auto tracked) {
+    constexpr bool kTrack = decltype(tracked)::value;
+    constexpr int S = A::kWide ? 2 : 4;  // taps a step: what the registers hold
+    typedef float vec __attribute__((ext_vector_type(S)));
+    typedef __attribute__((address_space(3))) vec lds_vec;
+    const int tid = here(threadIdx.x), j = tid & 31, h = (tid >> 5) & 1;
+    const lds_f32* xb = (const lds_f32*)&xs[buf][(wp * 2 + h) * RP][0];
+    const lds_f32* wb = (const lds_f32*)&ws[buf][wm * RM * 32 + j][0];
+    float nf[RM][RP];
 #pragma unroll
     for (int m = 0; m < RM; ++m)
 #pragma unroll
-      for (int r = 0; r < RP; ++r) out[m][r] = A::value(acc[m][r]);
-  }
-  if (!fits) {  // uniform over the workgroup
-    __syncthreads();
+      for (int r = 0; r < RP; ++r) nf[m][r] = kept ? nonfinite[m * RP + r][tid] : 0.0f;
+#pragma unroll 1
+    for (int t0 = 0; t0 < nt; t0 += S) {
+      vec xv[RP], wv[RM];
 #pragma unroll
-    for (int m = 0; m < RM; ++m)
+      for (int r = 0; r < RP; ++r) xv[r] = *(const lds_vec*)(xb + r * kRow + t0);
 #pragma unroll
-      for (int r = 0; r < RP; ++r) out[m][r] = 0.0f;
-    run(std::true_type{}, nothing, [&](const float(&xv)[RP], const float(&wv)[RM]) {
+      for (int m = 0; m < RM; ++m)
+        wv[m] = *(const lds_vec*)(wb + m * 32 * kRow + (S == 2 ? t0 ^ 2 : t0));
+      auto w_of = [&](int m, int t) { return wv[m][S == 2 ? t : t ^ 2]; };
+      typename A::Acc before[RM][RP];
+      float track = 0.0f;
 #pragma unroll
       for (int m = 0; m < RM; ++m)
 #pragma unroll
-        for (int r = 0; r < RP; ++r) out[m][r] = A::mac_checked(out[m][r], wv[m], xv[r]);
-    });
+        for (int r = 0; r < RP; ++r) before[m][r] = acc[m][r];
+#pragma unroll
+      for (int t = 0; t < S; ++t)
+#pragma unroll
+        for (int m = 0; m < RM; ++m) {
+          const float wt = w_of(m, t), wk = A::prescale(wt);
+#pragma unroll
+          for (int r = 0; r < RP; ++r) {
+            float p = A::product(wt, wk, xv[r][t]);
+            // an infinity that came through the product as one becomes NaN
+            if constexpr (A::kRtz || A::kExact) p = __builtin_fmaf(p, 0.0f, p);
+            acc[m][r] = A::template add<kTrack>(acc[m][r], p, track);
+          }
+        }
+      if (!kTrack || !__any(!(track < __uint_as_float(A::kOverflow)))) {
+#pragma unroll
+        for (int t = 0; t < S; ++t)
+#pragma unroll
+          for (int m = 0; m < RM; ++m)
+#pragma unroll
+            for (int r = 0; r < RP; ++r) nf[m][r] = __builtin_fmaf(w_of(m, t), xv[r][t], nf[m][r]);
+        continue;
+      }
+      float out[RM][RP];
+#pragma unroll
+      for (int m = 0; m < RM; ++m)
+#pragma unroll
+        for (int r = 0; r < RP; ++r)
+          out[m][r] = A::finite(nf[m][r]) ? A::value(before[m][r]) : nf[m][r];
+#pragma unroll 1
+      for (int t = t0; t < t0 + S; ++t) {
+        float x1[RP], w1[RM];
+#pragma unroll
+        for (int r = 0; r < RP; ++r) x1[r] = xb[r * kRow + t];
+#pragma unroll
+        for (int m = 0; m < RM; ++m) w1[m] = wb[m * 32 * kRow + (t ^ 2)];
+#pragma unroll
+        for (int m = 0; m < RM; ++m)
+#pragma unroll
+          for (int r = 0; r < RP; ++r) out[m][r] = A::mac_checked(out[m][r], w1[m], x1[r]);
+      }
+#pragma unroll
+      for (int m = 0; m < RM; ++m)
+#pragma unroll
+        for (int r = 0; r < RP; ++r) {
+          const bool ok = A::finite(out[m][r]);
+          nf[m][r] = ok ? 0.0f : out[m][r];
+          acc[m][r] = A::scaled(ok ? out[m][r] : __builtin_nanf(""));
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int r = 0; r < RP; ++r) nonfinite[m * RP + r][tid] = nf[m][r];
+    kept = true;
+  };
+
+  // All chunks in order: step ch computes chunk ch and stages chunk ch + 1; the
+  // first only stages.
+  __syncthreads();
+  Chunk nx{0, 0, 0, 0, kFlat ? min(32, taps) : min(32, p.C)};
+  int nq = 0;  // groups of four taps of the chunk to compute
+  Raw raw;
+  for (int ch = -1; ch < nch; ++ch) {
+    const bool more = ch + 1 < nch;
+    if (more) fetch(nx, raw);
+    const lds_f32* xb = (const lds_f32*)&xs[ch & 1][(wp * 2 + h) * RP][0];
+    const lds_f32* wb = (const lds_f32*)&ws[ch & 1][wm * RM * 32 + j][0];
+    auto load = [&](int q, f32x4(&xv)[RP], f32x4(&wv)[RM]) {
+#pragma unroll
+      for (int r = 0; r < RP; ++r) xv[r] = *(const lds_f32x4*)(xb + r * kRow + 4 * q);
+#pragma unroll
+      for (int m = 0; m < RM; ++m) wv[m] = *(const lds_f32x4*)(wb + m * 32 * kRow + 4 * q);
+    };
+    // (another wave may have staged the next chunk by now: its operands then count
+    // as well, which is on the safe side)
+    uint32_t sx = 0u, sw = 0u, watch = 0u;
+    if (nq > 0) sx = seen[0], sw = seen[1], watch = seen[2];
+    auto fast_chunk = [&] {
+      // operands of the next four taps are requested before this four's MACs
+      f32x4 xa[RP], wa[RM], xc[RP], wc[RM];
+      load(0, xa, wa);
+      int q = 0;
+      for (; q + 2 <= nq; q += 2) {
+        load(q + 1, xc, wc);
+        four(xa, wa);
+        load(q + 2 < nq ? q + 2 : q, xa, wa);
+        four(xc, wc);
+      }
+      if (q < nq) four(xa, wa);
+    };
+    // The chunk's route, from the sums before it: 0 the fast one, 1 with care for
+    // infinities and NaN, 2 for sums that leave the range as well.
+    auto route = [&](const typename A::Acc(&sum)[RM][RP]) {
+      sx = __builtin_amdgcn_readfirstlane(sx);
+      sw = __builtin_amdgcn_readfirstlane(sw);
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(watch) <= (uint32_t)ch, 1)) return 0;
+      const float big = __uint_as_float(decode_scaled<A::wE, A::wI, A::kScaleX, false>(sx)) *
+                        __uint_as_float(decode_scaled<A::wE, A::wI, A::kScaleW, false>(sw));
+      float a = 0.0f;
+#pragma unroll
+      for (int m = 0; m < RM; ++m)
+#pragma unroll
+        for (int r = 0; r < RP; ++r) A::track_max(a, A::magnitude(sum[m][r]), 0.0f);
+      if (__any(!(a + 32.0f * (big * pow2f(-A::kLift)) < A::kRoom * pow2f(A::kTop + A::kScale))))
+        return 2;
+      return __builtin_amdgcn_readfirstlane(seen[3]) > (uint32_t)ch ? 1 : 0;
+    };
+    if constexpr (RM * RP <= 4) {
+      // With few chains a wave the answer's latency would be waited for: the chunk
+      // is computed first and again where it needs care (one kind: the code between
+      // the staging and the barrier stays short).
+      if (nq > 0) {
+        typename A::Acc before[RM][RP];
+#pragma unroll
+        for (int m = 0; m < RM; ++m)
+#pragma unroll
+          for (int r = 0; r < RP; ++r) before[m][r] = acc[m][r];
+        fast_chunk();
+        if (__builtin_expect(route(before) != 0, 0)) {
+#pragma unroll
+          for (int m = 0; m < RM; ++m)
+#pragma unroll
+            for (int r = 0; r < RP; ++r) acc[m][r] = before[m][r];
+          careful_chunk(ch & 1, 4 * nq, std::true_type{});
+        }
+      }
+    } else if (nq > 0) {
+      const int kind = route(acc);
+      if (kind == 0)
+        fast_chunk();
+      else if (kind == 1)
+        careful_chunk(ch & 1, 4 * nq, std::false_type{});
+      else
+        careful_chunk(ch & 1, 4 * nq, std::true_type{});
+    }
+    if (more) stage(nx, raw, ch + 1, sx, sw);
+    nq = (nx.nc + 3) >> 2;
+    advance(nx);
+    __syncthreads();
+  }
+  float out[RM][RP];
+#pragma unroll
+  for (int m = 0; m < RM; ++m)
+#pragma unroll
+    for (int r = 0; r < RP; ++r) out[m][r] = A::value(acc[m][r]);
+  if (kept) {
+#pragma unroll
+    for (int m = 0; m < RM; ++m)
+#pragma unroll
+      for (int r = 0; r < RP; ++r) {
+        const float nf = nonfinite[m * RP + r][tid];
+        if (!A::finite(nf)) out[m][r] = nf;
+      }
   }
 
   // Epilogue: activation, conversion to the output format, store. Lane j of a
@@ -553,7 +736,7 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
 template <class V>
 __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __restrict__ in,
                                                             uint32_t* __restrict__ out,
-                                                            PoolParams p, float bound) {
+                                                            PoolParams p) {
   using A = ValueMath<V>;
   constexpr int NIN = V::NIN, NOUT = V::NOUT, kAhead = 8, kSign = V::wE + V::wF_IN;
   constexpr bool kHigh = NIN > 16;
@@ -570,52 +753,56 @@ __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __re
   const int lo = min(l, NIN - 1), hi = min(l + 16, NIN - 1);
   const RowT rt = row_transpose_setup(l);
   const PoolPairs pairs{(uint32_t)p.HW};
-  uint32_t mx = 0u, any = 0u;
-  // add(x) for every position in order
-  auto walk = [&](auto checked, auto&& add) {
-    constexpr bool kChecked = decltype(checked)::value;
-    for (uint32_t s0 = 0; pairs.more(s0); s0 += kAhead) {
-      uint32_t P[kAhead], Q[kAhead];
-#pragma unroll
-      for (int k = 0; k < kAhead; ++k) {
-        const uint32_t* at = src + (size_t)pairs.at(s0 + k, row & 1) * step;
-        P[k] = at[lo];
-        Q[k] = kHigh ? at[hi] : 0u;
-      }
-#pragma unroll
-      for (int k = 0; k < kAhead; ++k) {
-        const bool have = pairs.have(s0 + k, row & 1);
-        // past the end: -0, which changes no sum
-        P[k] = have ? (l < NIN ? P[k] : 0u) : (l == kSign ? ~0u : 0u);
-        if constexpr (kHigh) Q[k] = have ? (l + 16 < NIN ? Q[k] : 0u) : (l + 16 == kSign ? ~0u : 0u);
-        any |= kHigh ? Q[k] : P[k];
-      }
-      row_transpose(P, rt);
-      if constexpr (kHigh) row_transpose(Q, rt);
-#pragma unroll
-      for (int k = 0; k < kAhead; ++k) {
-        uint32_t a, b;
-        stage16_from_pairs(P[k], Q[k], a, b);
-        const uint32_t va = decode_scaled<V::wE, V::wF_IN, kChecked ? 0 : A::kScale, kChecked>(a);
-        const uint32_t vb = decode_scaled<V::wE, V::wF_IN, kChecked ? 0 : A::kScale, kChecked>(b);
-        mx = max(mx, max(va & 0x7FFFFFFFu, vb & 0x7FFFFFFFu));
-        add(__uint_as_float(va));
-        add(__uint_as_float(vb));
-      }
-    }
-  };
+  // Every position in order, 2 kAhead at a time. Where those hold an infinity or NaN
+  // or their sums may leave the range, and once a sum of the wave is infinite or
+  // NaN, they are added with the range checks written out.
+  static_assert(2 * kAhead <= 32);  // of kRoom
+  uint32_t mx = 0u;
   A::set_mode();
   typename A::Acc acc = 0;
-  float track = 0.0f;
-  walk(std::false_type{}, [&](float x) { acc = A::add(acc, x, track); });
-  float v = A::value(acc);
-  const bool bad = !(__uint_as_float(mx) * pow2f(-A::kScale) < bound) ||
-                   (l == ((NIN - 1) & 15) && any != 0u) ||
-                   (A::kTrack && __float_as_uint(track) >= A::kOverflow);
-  if (__any(bad)) {  // infinities, NaN, or sums that may leave the range
-    v = 0.0f;
-    walk(std::true_type{}, [&](float x) { v = A::add_checked(v, x); });
+  float nothing = 0.0f;
+  for (uint32_t s0 = 0; pairs.more(s0); s0 += kAhead) {
+    uint32_t P[kAhead], Q[kAhead], any = 0u;
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const uint32_t* at = src + (size_t)pairs.at(s0 + k, row & 1) * step;
+      P[k] = at[lo];
+      Q[k] = kHigh ? at[hi] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      const bool have = pairs.have(s0 + k, row & 1);
+      // past the end: -0, which changes no sum
+      P[k] = have ? (l < NIN ? P[k] : 0u) : (l == kSign ? ~0u : 0u);
+      if constexpr (kHigh) Q[k] = have ? (l + 16 < NIN ? Q[k] : 0u) : (l + 16 == kSign ? ~0u : 0u);
+      any |= kHigh ? Q[k] : P[k];
+    }
+    const bool special = __any(l == ((NIN - 1) & 15) && any != 0u);
+    row_transpose(P, rt);
+    if constexpr (kHigh) row_transpose(Q, rt);
+    float x[2 * kAhead];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) {
+      uint32_t a, b;
+      stage16_from_pairs(P[k], Q[k], a, b);
+      const uint32_t va = decode_scaled<V::wE, V::wF_IN, A::kScale, true>(a);
+      const uint32_t vb = decode_scaled<V::wE, V::wF_IN, A::kScale, true>(b);
+      mx = max(mx, max(va & 0x7FFFFFFFu, vb & 0x7FFFFFFFu));
+      x[2 * k] = __uint_as_float(va);
+      x[2 * k + 1] = __uint_as_float(vb);
+    }
+    const float most = A::magnitude(acc) + (float)(2 * kAhead) * __uint_as_float(mx);
+    if (__any(special || !(most < A::kRoom * pow2f(A::kTop + A::kScale)))) {
+      float v = A::value(acc);
+#pragma unroll
+      for (int k = 0; k < 2 * kAhead; ++k) v = A::add_checked(v, x[k] * pow2f(-A::kScale));
+      acc = A::scaled(v);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 2 * kAhead; ++k) acc = A::template add<false>(acc, x[k], nothing);
+    }
   }
+  const float v = A::value(acc);
   // the product of two accumulator values is exact in float32
   const float scale =
       __uint_as_float(decode_scaled<V::wE, V::wF_ACC, 0, true>(p.scale));
@@ -647,7 +834,9 @@ hipError_t launch_value_tile(const uint32_t* ifm, const uint32_t* w, uint32_t* o
 template <class V>
 hipError_t launch_value(const uint32_t* ifm, const uint32_t* w, uint32_t* ofm, const ConvParams& p,
                         int tile, hipStream_t stream) {
-  const float bound = ValueMath<V>::bound((double)p.KH * p.KW * p.C);
+  // of the product of the largest x and w as the kernel scales them
+  using A = ValueMath<V>;
+  const float bound = (float)ldexp(A::bound((double)p.KH * p.KW * p.C), A::kScale + A::kLift);
   switch (tile) {
     case kTile112x64: return launch_value_tile<V, 1, 7, 8, 2>(ifm, w, ofm, p, bound, stream);
     case kTile56x64: return launch_value_tile<V, 1, 7, 4, 2>(ifm, w, ofm, p, bound, stream);
