@@ -84,6 +84,13 @@ struct ValueMath {
   static constexpr int kScaleW = kScale - kScaleX + kLift;
   // exponent of the first power of two out of range
   static constexpr int kTop = (1 << wE) - kBias;
+  // What the steps rest on (and product on a bound of its own): products and sums
+  // scaled as above, and the plain sum of products of the slower route, stay in
+  // float32's range; an accumulator value is a float32 with bits to round at. The
+  // kernels round their result once more, by quantize_narrow, whose additions follow
+  // the hardware's rounding mode: set_mode makes that the variant's own.
+  static_assert(wE >= 2 && wE <= 6, "scaled values and products leave float32's range");
+  static_assert(wA >= wI && wA <= 22 && V::wF_OUT <= 22, "no bit of float32 to round at");
   // The smallest sum out of range before its rounding, scaled: to nearest, half a
   // unit in the last place below 2^kTop rounds up to it (a tie goes to 2^kTop, whose
   // last place is even).
@@ -119,6 +126,7 @@ struct ValueMath {
   static __device__ __forceinline__ float product(float w, float wk, float x) {
     if constexpr (kRtz) return kExact ? w * x : trunc(w * x);
     if constexpr (kExact) return w * x;
+    static_assert(kRtz || kExact || wI <= 10, "2^k w x is no even multiple of c's last place");
     const float c = wk * x;
     const float d = __builtin_fmaf(-w, x, c);
     const float r = c - d;
@@ -413,7 +421,7 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
 #pragma unroll
     for (int i = 0; i < WS; ++i) {
       const int t = 4 * ((wave + i * NW) & 7) + grp;
-      static_assert(A::wE + A::wI < 16);
+      static_assert(A::wE + A::wI < 16);  // the sign is among the first word's planes
       const uint32_t fill = l == A::wE + A::wI ? ~0u : 0u;  // -0
       P[X + i] = t < c.nc ? (l < NIN ? raw.w[i][0] : 0u) : fill;
       Q[X + i] = 0u;
@@ -804,6 +812,7 @@ __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __re
   }
   const float v = A::value(acc);
   // the product of two accumulator values is exact in float32
+  static_assert(2 * (V::wF_ACC + 1) <= 24);
   const float scale =
       __uint_as_float(decode_scaled<V::wE, V::wF_ACC, 0, true>(p.scale));
   uint32_t code[2] = {quantize_narrow(__float_as_uint(v * scale), V::wE, V::wF_OUT), 0u};
