@@ -374,7 +374,7 @@ def split_asm(wE, wi, wa, rnd, cache, compact=False):
     return cache[key] if cache[key]["text"] is not None else None
 
 
-def value_ops(wi, wa, rnd):
+def value_ops(wE, wi, wa, rnd):
     """Operations of one multiply-add of the kernel on float32 values
     (csrc/value.hpp, ValueMath), float64 ones counted twice: the product, its
     rounding unless it is exact, the sum and its rounding."""
@@ -382,9 +382,15 @@ def value_ops(wi, wa, rnd):
     if rnd == variants.RTZ:
         return 3 if exact else 4
     if wa > 10:
-        return 13 if exact else 16
-    lift = not exact and 23 - wa < 15
-    return 5 if exact else 8 if lift else 7
+        # the term's conversion, a fused multiply-add and a product (the
+        # flush), a product and two differences (the rounding), in float64
+        total = 12
+    else:
+        total = 4  # a sum, a product and two differences
+    k, bias = 23 - wa, (1 << (wE - 1)) - 1
+    if exact:
+        return total + 1
+    return total + 3 + (k < bias)  # ValueMath.kLift
 
 
 def generate(verbose=True):
@@ -614,7 +620,7 @@ hipError_t launch_pool_{tag}(const uint32_t* in, uint32_t* out, const PoolParams
     reg.append("const ConvVariant kConvVariants[] = {")
     for v, tag, ops, pops, aops, has_split, has_compact in reg_conv:
         reg.append(f"  {{{v[0]}, {v[1]}, {v[2]}, {v[3]}, {v[4]}, {v[5]}, {has_split}, "
-                   f"{has_compact}, {ops}, {pops}, {aops}, {value_ops(*v[1:3], v[5])}, "
+                   f"{has_compact}, {ops}, {pops}, {aops}, {value_ops(*v[:3], v[5])}, "
                    f"launch_conv_{tag}}},")
     reg.append("};")
     reg.append(f"const int kNumConvVariants = {len(reg_conv)};")

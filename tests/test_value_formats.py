@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from paper_2007_06563_amd import build
+from paper_2007_06563_amd import build, variants
 
 SRC = """
 #include "value.hpp"
@@ -41,3 +41,16 @@ def test_conditions_of_the_arithmetic(tmp_path, fmt, what, ok):
                        capture_output=True, text=True)
     assert (r.returncode == 0) == ok, r.stderr[-2000:]
     assert ok or "static assertion failed" in r.stderr, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("fmt,ops", [
+    ((5, 3, 4, variants.RNE), 7), ((5, 9, 10, variants.RNE), 8), ((5, 3, 7, variants.RNE), 5),
+    ((5, 10, 11, variants.RNE), 16), ((5, 10, 21, variants.RNE), 13), ((5, 3, 4, variants.RTZ), 4),
+    ((5, 3, 7, variants.RTZ), 3),
+    ((4, 9, 10, variants.RNE), 7),  # a bias of 7: products need no scaling back
+], ids=str)
+def test_operation_counts(fmt, ops):
+    """The count that AUTO's estimate and the benchmark's bound use, by hand: product
+    1; its rounding 2, scaled back 1 more where 2^(23 - wF) is below 2^bias; a sum and
+    its rounding 4, in float64 six of two each; toward zero 1 for each step."""
+    assert build.value_ops(*fmt) == ops
