@@ -735,7 +735,7 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
 
 // Global average pooling on values, for few (image, channel word) groups: the
 // bitsliced kernel gives a group to a lane, whose chain of H W adds of some 130
-// instructions then sets the time (16x7x7x1024, (5,4): 256 such lanes, 15.4 us).
+// instructions then sets the time (16x7x7x1024, (5,4): 512 such lanes, 15.4 us).
 // Here a half wave takes a group, a lane a channel: a set (see the convolution)
 // is two positions of the wave's two groups, its words are loaded kAhead sets
 // together, and each value is added in four operations. About 10 instructions
@@ -763,12 +763,12 @@ __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __re
   const PoolPairs pairs{(uint32_t)p.HW};
   // Every position in order, 2 kAhead at a time. Where those hold an infinity or NaN
   // or their sums may leave the range, and once a sum of the wave is infinite or
-  // NaN, they are added with the range checks written out.
+  // NaN, they are added again with the range checks written out.
   static_assert(2 * kAhead <= 32);  // of kRoom
   uint32_t mx = 0u;
   A::set_mode();
   typename A::Acc acc = 0;
-  float nothing = 0.0f;
+  float none = 0.0f;
   for (uint32_t s0 = 0; pairs.more(s0); s0 += kAhead) {
     uint32_t P[kAhead], Q[kAhead], any = 0u;
 #pragma unroll
@@ -788,26 +788,28 @@ __global__ __launch_bounds__(256) void avgpool_value_kernel(const uint32_t* __re
     const bool special = __any(l == ((NIN - 1) & 15) && any != 0u);
     row_transpose(P, rt);
     if constexpr (kHigh) row_transpose(Q, rt);
-    float x[2 * kAhead];
+    const typename A::Acc before = acc;
 #pragma unroll
     for (int k = 0; k < kAhead; ++k) {
       uint32_t a, b;
       stage16_from_pairs(P[k], Q[k], a, b);
-      const uint32_t va = decode_scaled<V::wE, V::wF_IN, A::kScale, true>(a);
-      const uint32_t vb = decode_scaled<V::wE, V::wF_IN, A::kScale, true>(b);
+      P[k] = a;
+      Q[k] = b;
+      const uint32_t va = decode_scaled<V::wE, V::wF_IN, A::kScale, false>(a);
+      const uint32_t vb = decode_scaled<V::wE, V::wF_IN, A::kScale, false>(b);
       mx = max(mx, max(va & 0x7FFFFFFFu, vb & 0x7FFFFFFFu));
-      x[2 * k] = __uint_as_float(va);
-      x[2 * k + 1] = __uint_as_float(vb);
+      acc = A::template add<false>(acc, __uint_as_float(va), none);
+      acc = A::template add<false>(acc, __uint_as_float(vb), none);
     }
-    const float most = A::magnitude(acc) + (float)(2 * kAhead) * __uint_as_float(mx);
-    if (__any(special || !(most < A::kRoom * pow2f(A::kTop + A::kScale)))) {
-      float v = A::value(acc);
+    const float most = A::magnitude(before) + (float)(2 * kAhead) * __uint_as_float(mx);
+    if (__builtin_expect(__any(special || !(most < A::kRoom * pow2f(A::kTop + A::kScale))), 0)) {
+      float v = A::value(before);
 #pragma unroll
-      for (int k = 0; k < 2 * kAhead; ++k) v = A::add_checked(v, x[k] * pow2f(-A::kScale));
+      for (int k = 0; k < kAhead; ++k) {
+        v = A::add_checked(v, __uint_as_float(decode_scaled<V::wE, V::wF_IN, 0, true>(P[k])));
+        v = A::add_checked(v, __uint_as_float(decode_scaled<V::wE, V::wF_IN, 0, true>(Q[k])));
+      }
       acc = A::scaled(v);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 2 * kAhead; ++k) acc = A::template add<false>(acc, x[k], nothing);
     }
   }
   const float v = A::value(acc);
