@@ -261,7 +261,10 @@ static bool value_tile_ok(const ConvParams& p, const ConvVariant& v, int k) {
 // AUTO's choice between the bitsliced kernel shape `algo` and the kernel on
 // float32 values: the tile of the latter, or -1. Both sides are estimated in
 // microseconds from the layer's sizes and the variant's operation counts; every
-// constant below was measured on MI355X (256 CUs) and is not sensitive.
+// constant below was measured on MI355X (256 CUs). Of 110 layers drawn over sizes,
+// formats and roundings and 64 of 1 to 15 channels, none that it runs on values ran
+// slower there than bitsliced; 12 would have gained 10 to 50 % from the other kernel
+// or tile.
 //  - On values, a workgroup computes one tile; tiles beyond the number of CUs
 //    take further rounds. A round costs `chains` accumulator chains a SIMD, at
 //    1.26 ns a tap and operation each (112x64 tiles: 8x56x56x64 -> 64, 576 taps
@@ -273,6 +276,11 @@ static bool value_tile_ok(const ConvParams& p, const ConvVariant& v, int k) {
 //    netlists' at 2.48 ns in the compact kernel, or two rounds of the split one;
 //    more: the chip's share of the fused netlist at 1.73 ns an instruction
 //    (4x224x224x3 -> 64: 73 us).
+//  - Fewer than kFlatC channels have the same constants, though their staging
+//    gathers each code bit by bit: 1x224x224x3 -> 64, 7x7 stride 2, (5,3): 39.6 us on
+//    values, 57.5 bitsliced; 4 images: bitsliced, 95.5 against 114.9.
+//  - Inputs are taken to be ordinary ones: the host does not know them (value.hpp
+//    has the time of infinities, NaN and overflow).
 static int value_plan(const ConvParams& p, const ConvVariant& v, int algo, int cus) {
   const double t = (double)p.KH * p.KW * p.C;
   struct Cost {

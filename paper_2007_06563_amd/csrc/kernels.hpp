@@ -145,9 +145,10 @@ constexpr int kAlgoValue = 4;
 constexpr int kTile112x64 = 0, kTile56x64 = 1, kTile32x64 = 2, kTile32x32 = 3, kTile16x32 = 4;
 // Pooling takes its kernel on values up to this many (image, channel word)
 // groups: its time grows with them, the bitsliced kernel's is that of one lane's
-// chain up to some 32,000. Maps of 7x7, on values / bitsliced: (5,3) 4096 groups
-// 8.6 / 13.9 us, 8192 14.5 / 14.0; (5,11) 11.0 / 29.4 and 19.1 / 29.6; other
-// formats lie between, and longer maps favour it more.
+// chain up to some 32,000. Maps of 7x7, kernel trace in us: (5,3) on values 512
+// groups 6.1, 4096 9.0, 6144 11.6 (all inputs NaN 8.8, 13.8, 18.3), bitsliced 13.9 to
+// 14.9 whatever the inputs; (5,11) 8.5, 12.0, 16.4 (11.6, 16.3, 21.3) and 31. Longer
+// maps favour it more.
 constexpr int64_t kPoolValueGroups = 6144;
 constexpr int kFlatC = 16;  // fewer channels than this: chunks of taps across pixels
 

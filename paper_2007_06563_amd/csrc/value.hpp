@@ -6,8 +6,9 @@
 // 6.3 a value, and its smallest piece of work is a wave of 2,048 accumulator
 // chains that no reordering may split; a layer of a few hundred such waves
 // leaves most of the chip idle. One float32 operation per step of the MAC takes
-// 7 instructions a value (4 rounding toward zero) whatever the fraction width,
-// and its smallest piece is 64 chains.
+// 7 instructions a value (4 rounding toward zero) up to 10 fraction bits in the
+// accumulator, 13 to 16 above to nearest (float64 ones counted twice), and its
+// smallest piece is 64 chains.
 //
 // How float32 gives the format's own results. A value of (wE, wF) is an exact
 // float32. Operands are scaled by powers of two, so that the format's smallest
@@ -61,6 +62,8 @@ namespace hobflops {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) float lds_f32;
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 
 __device__ __forceinline__ float pow2f(int e) { return __int_as_float((e + 127) << 23); }
 
@@ -618,10 +621,10 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
 #pragma unroll
       for (int m = 0; m < RM; ++m) wv[m] = *(const lds_f32x4*)(wb + m * 32 * kRow + 4 * q);
     };
-    // (another wave may have staged the next chunk by now: its operands then count
-    // as well, which is on the safe side)
-    uint32_t sx = 0u, sw = 0u, watch = 0u;
-    if (nq > 0) sx = seen[0], sw = seen[1], watch = seen[2];
+    // What is known of chunk ch's operands. Another wave may have staged the next
+    // chunk by now: its operands then count as well, which is on the safe side.
+    const u32x4 now = *(volatile lds_u32x4*)&seen[0];
+    uint32_t sx = 0u, sw = 0u;  // now's, for the staging
     auto fast_chunk = [&] {
       // operands of the next four taps are requested before this four's MACs
       f32x4 xa[RP], wa[RM], xc[RP], wc[RM];
@@ -638,9 +641,9 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
     // The chunk's route, from the sums before it: 0 the fast one, 1 with care for
     // infinities and NaN, 2 for sums that leave the range as well.
     auto route = [&](const typename A::Acc(&sum)[RM][RP]) {
-      sx = __builtin_amdgcn_readfirstlane(sx);
-      sw = __builtin_amdgcn_readfirstlane(sw);
-      if (__builtin_expect(__builtin_amdgcn_readfirstlane(watch) <= (uint32_t)ch, 1)) return 0;
+      sx = __builtin_amdgcn_readfirstlane(now.x);
+      sw = __builtin_amdgcn_readfirstlane(now.y);
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane(now.z) <= (uint32_t)ch, 1)) return 0;
       const float big = __uint_as_float(decode_scaled<A::wE, A::wI, A::kScaleX, false>(sx)) *
                         __uint_as_float(decode_scaled<A::wE, A::wI, A::kScaleW, false>(sw));
       float a = 0.0f;
@@ -650,12 +653,13 @@ __global__ __launch_bounds__(64 * WP * WM) void conv2d_value_kernel(
         for (int r = 0; r < RP; ++r) A::track_max(a, A::magnitude(sum[m][r]), 0.0f);
       if (__any(!(a + 32.0f * (big * pow2f(-A::kLift)) < A::kRoom * pow2f(A::kTop + A::kScale))))
         return 2;
-      return __builtin_amdgcn_readfirstlane(seen[3]) > (uint32_t)ch ? 1 : 0;
+      return __builtin_amdgcn_readfirstlane(now.w) > (uint32_t)ch ? 1 : 0;
     };
-    if constexpr (RM * RP <= 4) {
-      // With few chains a wave the answer's latency would be waited for: the chunk
-      // is computed first and again where it needs care (one kind: the code between
-      // the staging and the barrier stays short).
+    if constexpr (T::kWaves <= 8) {
+      // Two waves a SIMD would wait for the route's answer: the chunk is computed first
+      // and again where it needs care (14x14x256 -> 256 at batch 16, 56x64 tiles: 310
+      // us with the route chosen before, 303). Care is of one kind here, as two of them
+      // between staging and barrier cost 4 %.
       if (nq > 0) {
         typename A::Acc before[RM][RP];
 #pragma unroll
