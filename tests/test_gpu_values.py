@@ -240,8 +240,8 @@ def test_chunks_that_need_care(v):
                                (5, 10, 21, 21, 0, 0), (4, 3, 7, 7, 0, 0)], ids=variants.conv_tag)
 def test_large_tiles(v):
     """Layers of many workgroups, ragged at both ends, in the 112x64, 56x64 and 32x64
-    tiles: sums in float64 and in float32, products rounded and exact, toward zero,
-    sums tracked."""
+    tiles: sums in float64 and in float32, products rounded and exact, toward zero, a
+    short exponent under a long fraction."""
     hf = need_gpu()
     wE, wi, wa, wo, act, rnd = v
     for N, H, W, C, M in ((3, 47, 50, 64, 192), (2, 29, 31, 96, 250)):
